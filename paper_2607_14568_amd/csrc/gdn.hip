@@ -1487,119 +1487,55 @@ __global__ __launch_bounds__(NT_CHAIN) __attribute__((amdgpu_waves_per_eu(1, 2))
 }
 
 // ------------------------------------------------------------------ bf16 chunk terms
-// One workgroup (4 waves) per (chunk slot, head), bf16 io.  Produces for the
-// state chain gamma_r and exp(G_n - G_r), and in MFMA fragment order
+// One wave per (chunk slot, head), bf16 io.  Produces for the state chain
+// gamma_r and exp(G_n - G_r), and in MFMA fragment order
 //     W  = diag(D) T diag(beta)     lower triangular, 6 fragments
 //     P' = P T diag(beta)           lower triangular, 6 fragments
 // with T = (I + A)^{-1}.
-// Stages: K and Q arrive by buffer loads to LDS (rows past a chunk read as
-// zero); prefix sums of g in fp64 log2 units (every decay factor is one exp2
-// of an fp64 difference); each wave forms its share of the lower 16x16 blocks
-// of K K^T and Q K^T with all its operands in registers, so the tiles' LDS
-// space holds A, P and T afterwards; T's diagonal blocks by forward
-// substitution with the rows of A in registers; its off-diagonal blocks one
-// block diagonal at a time by fp32 MFMA block products; the fragments of W and
-// P' from a bf16 copy of T.
-template <int DK, int W, bool NORM>
-__device__ __forceinline__ void gram_blocks(const bf16_t* sK, const bf16_t* sQ, const double* sGl, const float* sB,
-                                            const float* sSk, const float* sSq, int l16, int lg, floatx4 (&ablk)[3],
-                                            floatx4 (&pblk)[3]) {
-    constexpr int NCH = DK / 8, NKD = DK / 32;
-    // lower 16x16 blocks (bi, bj): KK^T takes entries W, W+4, ..; QK^T entries (W+2)%4, ..
-    constexpr int BI[10] = {0, 1, 1, 2, 2, 2, 3, 3, 3, 3};
-    constexpr int BJ[10] = {0, 0, 1, 0, 1, 2, 0, 1, 2, 3};
-    constexpr int QW = (W + 2) % 4;
-    constexpr int NA = W < 2 ? 3 : 2, NP = QW < 2 ? 3 : 2;
-    auto swz = [](int r) { return ((4 * (r & 3)) | ((r >> 2) & 3)) & (NCH - 1); };
-    auto kq = [&](int r, int cc) { return r * DK + (((cc >> 3) ^ swz(r)) << 3) + (cc & 7); };
-    bf16x8 kf[4][NKD];
-#pragma unroll
-    for (int rb = 0; rb < 4; ++rb)
-#pragma unroll
-        for (int kk = 0; kk < NKD; ++kk) kf[rb][kk] = *reinterpret_cast<const bf16x8*>(sK + kq(16 * rb + l16, 32 * kk + 8 * lg));
-    bf16x8 qf[NP][NKD];
-#pragma unroll
-    for (int j = 0; j < NP; ++j)
-#pragma unroll
-        for (int kk = 0; kk < NKD; ++kk)
-            qf[j][kk] = *reinterpret_cast<const bf16x8*>(sQ + kq(16 * BI[QW + 4 * j] + l16, 32 * kk + 8 * lg));
-#pragma unroll
-    for (int j = 0; j < NA; ++j) {
-        const int bi = BI[W + 4 * j], bj = BJ[W + 4 * j];
-        floatx4 acc = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-        for (int kk = 0; kk < NKD; ++kk) acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf[bi][kk], kf[bj][kk], acc, 0, 0, 0);
-        const int i = 16 * bj + l16;
-        const double gi = sGl[i];
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            const int r = 16 * bi + 4 * lg + e;
-            const float gam = __builtin_amdgcn_exp2f((float)(sGl[r] - gi));
-            if constexpr (NORM) acc[e] *= sSk[r] * sSk[i];
-            ablk[j][e] = r > i ? sB[r] * gam * acc[e] : 0.f;
-        }
-    }
-#pragma unroll
-    for (int j = 0; j < NP; ++j) {
-        const int bi = BI[QW + 4 * j], bj = BJ[QW + 4 * j];
-        floatx4 acc = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-        for (int kk = 0; kk < NKD; ++kk) acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(qf[j][kk], kf[bj][kk], acc, 0, 0, 0);
-        const int i = 16 * bj + l16;
-        const double gi = sGl[i];
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            const int r = 16 * bi + 4 * lg + e;
-            const float gam = __builtin_amdgcn_exp2f((float)(sGl[r] - gi));
-            if constexpr (NORM) acc[e] *= sSq[r] * sSk[i];
-            pblk[j][e] = r >= i ? gam * acc[e] : 0.f;
-        }
-    }
-}
-
-template <int DK, int W>
-__device__ __forceinline__ void store_gram(float (*sA)[CH + 4], bf16_t (*sPb)[CH + 8], int l16, int lg,
-                                           const floatx4 (&ablk)[3], const floatx4 (&pblk)[3]) {
-    constexpr int BI[10] = {0, 1, 1, 2, 2, 2, 3, 3, 3, 3};
-    constexpr int BJ[10] = {0, 0, 1, 0, 1, 2, 0, 1, 2, 3};
-    constexpr int QW = (W + 2) % 4;
-    constexpr int NA = W < 2 ? 3 : 2, NP = QW < 2 ? 3 : 2;
-#pragma unroll
-    for (int j = 0; j < NA; ++j)
-#pragma unroll
-        for (int e = 0; e < 4; ++e) sA[16 * BI[W + 4 * j] + 4 * lg + e][16 * BJ[W + 4 * j] + l16] = ablk[j][e];
-#pragma unroll
-    for (int j = 0; j < NP; ++j)
-#pragma unroll
-        for (int e = 0; e < 4; ++e) sPb[16 * BI[QW + 4 * j] + 4 * lg + e][16 * BJ[QW + 4 * j] + l16] = from_f<bf16_t>(pblk[j][e]);
-}
-
-// LDS of one chunk-terms work item: phase 1 holds the K and Q tiles; phase
-// 2 reuses the space for A, T (fp32) and P (bf16), and T's bf16 copy over A
-template <int DK> struct TermsLds {
-    static constexpr int PA = CH + 4, PB = CH + 8;   // row pitches of the fp32 and bf16 64 x 64 matrices
-    static constexpr int SZ_TILES = 2 * CH * DK * 2;
-    static constexpr int SZ_MATS = 2 * CH * PA * 4 + CH * PB * 2;
-    __attribute__((aligned(16))) char r0[SZ_TILES > SZ_MATS ? SZ_TILES : SZ_MATS];
-    double sGl[CH];
-    __attribute__((aligned(16))) float sB[CH];
-    __attribute__((aligned(16))) float sD[CH];
-    float sSk[CH], sSq[CH];   // reciprocal row lengths of K and Q (PRE_L2)
+//
+// A chunk's terms are a serial chain of small products; spread over the four
+// waves of a workgroup, an item spent most of its time at the barriers between
+// them, and only three items fitted a CU's LDS.  Here a wave keeps a whole item
+// in its registers and shares nothing, so there is no barrier and a CU runs eight
+// items at once (two waves per SIMD: K and Q take 128 registers), each waiting
+// only for itself.  What crosses lanes goes through the wave's own LDS: G, beta
+// and the row lengths, the four diagonal blocks, and T's bf16 copy.  The kernel by
+// itself is then bound by memory (K and Q in, 13 KB out per item): 40.5 -> 30.7 us
+// for a prompt of 10240 tokens and 16 heads (117 MB, 3.8 TB/s), 62.7 -> 47.9 us for
+// 17481 packed tokens (200 MB, 4.2 TB/s; a large copy reaches 5.1).
+//
+// Blocks are 16 x 16; D layout: lane holds rows 4 lg + e of column l16 (what an
+// MFMA leaves).  K and Q rows are loaded straight into operand registers.
+//   A_mj (D layout) from K_m K_j^T, P_bj^T (D layout) from K_j Q_b^T, decays as
+//     exp2 of fp64 differences of the prefix sums, masked before use;
+//   T_jj by forward substitution, lane = 16 j + column;
+//   Y_jb = T_bj^T (D layout) = -T_jj^T sum_{j < m <= b} A_mj^T Y_mb on fp32
+//     MFMA: with contraction index 4 lg + kk the D layout of A_mj and of T_jj is
+//     the transposed first operand, and Y_mb is the second, so no value moves;
+//   W fragments are Y scaled (D layout of Y_jb = row l16, columns 4 lg + e of T);
+//   P'^T_{jb} = T^T P^T on bf16 MFMA: P^T packs from its accumulators, T^T comes
+//     from T's bf16 copy by transpose reads.
+struct TermsLds {
+    double G[CH];                                          // prefix sums of g, log2 units
+    __attribute__((aligned(16))) float B[CH];              // beta
+    float D[CH];                                           // exp2(G_n - G_r)
+    float Sk[CH], Sq[CH];                                  // reciprocal row lengths of K and Q (PRE_L2)
+    __attribute__((aligned(16))) float X[4][16][20];       // diagonal blocks: of A, then of T
+    __attribute__((aligned(16))) bf16_t Tb[CH][CH + 8];    // T, blocks on and below the diagonal
 };
 
-// Chunk terms of work item gi = chunk slot * H + head, by the 4 waves whose
-// threads are tid = 0..255.  store = false computes without writing (a
-// placeholder item that keeps a workgroup's two halves in step).  FUSED: every
+// Orders the wave's own LDS accesses for the compiler (the hardware keeps them in order).
+__device__ __forceinline__ void wave_lds_fence() { asm volatile("" ::: "memory"); }
+
+// Chunk terms of work item gi = chunk slot * H + head, by one wave.  FUSED: every
 // result is stored with cache-bypassing stores, then the slot's flag is set to
 // the call's epoch; and the item's V rows, which only the chain reads, are
-// copied into vsink (LDS nobody reads) so that they wait in L2 for the chain.
+// copied into vsink (1 KB of LDS nobody reads) so that they wait in L2 for the
+// chain.
 template <int DK, bool FUSED, bool NORM>
-__device__ __forceinline__ void chunk_terms_bf16(const Params& p, const long gi, TermsLds<DK>& lds, const int tid,
-                                                 const bool store, bf16_t* vsink = nullptr) {
-    constexpr int NCH = DK / 8;     // 16-byte chunks per K/Q row
-    constexpr int RPI = 64 / NCH;   // rows per 1 KB buffer load
-    constexpr int TILE = CH * DK;
-    constexpr int PA = TermsLds<DK>::PA, PB = TermsLds<DK>::PB;
+__device__ __forceinline__ void chunk_terms_bf16(const Params& p, const long gi, TermsLds& lds, const int lane,
+                                                 bf16_t* vsink = nullptr) {
+    constexpr int NKD = DK / 32;
     constexpr int AUX = FUSED ? 17 : 0;
     const int H = p.H;
     const int gc = (int)(gi / H), h = (int)(gi % H);
@@ -1622,41 +1558,27 @@ __device__ __forceinline__ void chunk_terms_bf16(const Params& p, const long gi,
     const long t0 = start + (long)c * CH;
     const int n = min(CH, len - c * CH);
     const long slot = (long)gc * H + h;
-
-    char* r0 = lds.r0;
-    double* sGl = lds.sGl;
-    float* sB = lds.sB;
-    float* sD = lds.sD;
-    float* sSk = lds.sSk;
-    float* sSq = lds.sSq;
-    bf16_t* sK = reinterpret_cast<bf16_t*>(r0);
-    bf16_t* sQ = sK + TILE;
-    float(*sA)[PA] = reinterpret_cast<float(*)[PA]>(r0);
-    float(*sTi)[PA] = reinterpret_cast<float(*)[PA]>(r0 + CH * PA * 4);
-    bf16_t(*sPb)[PB] = reinterpret_cast<bf16_t(*)[PB]>(r0 + 2 * CH * PA * 4);
-    bf16_t(*sTb)[PB] = reinterpret_cast<bf16_t(*)[PB]>(r0);
-
-    const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int l16 = lane & 15, lg = lane >> 4;
-    auto swz = [](int r) { return ((4 * (r & 3)) | ((r >> 2) & 3)) & (NCH - 1); };
 
-    {   // K and Q tiles straight into LDS; loads i = wave, wave + 4, ...
-        const bf16_t* gk = reinterpret_cast<const bf16_t*>(p.k);
-        const bf16_t* gq = reinterpret_cast<const bf16_t*>(p.q);
+    // K and Q rows as MFMA operands (rows past the chunk read as zeros)
+    bf16x8 kf[4][NKD], qf[4][NKD];
+    {
         const int HK = p.HK;   // q and k carry HK heads; this head reads key head h / G
         const long row0 = t0 * HK + h / p.G;
         const uint32_t bytes = (uint32_t)(((long)(n - 1) * HK + 1) * DK * 2);
-        const auto rk = rsrc(gk + row0 * DK, bytes);
-        const auto rq = rsrc(gq + row0 * DK, bytes);
-        for (int i = wave; i < NCH; i += 4) {
-            const int r = RPI * i + lane / NCH;
-            const int off = (r * HK * DK + (((lane % NCH) ^ swz(r)) << 3)) * 2;
-            bdma16(rk, sK + RPI * i * DK, off);
-            bdma16(rq, sQ + RPI * i * DK, off);
-        }
+        const auto rk = rsrc(reinterpret_cast<const bf16_t*>(p.k) + row0 * DK, bytes);
+        const auto rq = rsrc(reinterpret_cast<const bf16_t*>(p.q) + row0 * DK, bytes);
+        const int off = (l16 * HK * DK + 8 * lg) * 2, rstep = 16 * HK * DK * 2;
+#pragma unroll
+        for (int rb = 0; rb < 4; ++rb)
+#pragma unroll
+            for (int kk = 0; kk < NKD; ++kk) kf[rb][kk] = bload16(rk, off + rb * rstep + 64 * kk);
+#pragma unroll
+        for (int rb = 0; rb < 4; ++rb)
+#pragma unroll
+            for (int kk = 0; kk < NKD; ++kk) qf[rb][kk] = bload16(rq, off + rb * rstep + 64 * kk);
     }
-    if (wave == 0) {
-        // prefix sums of g in log2 units, fp64; padded rows: no decay, no write
+    {   // prefix sums of g in log2 units, fp64; padded rows: no decay, no write
         float gv = lane < n ? p.g[(t0 + lane) * H + h] : 0.f;
         float bv = lane < n ? p.beta[(t0 + lane) * H + h] : 0.f;
         if ((p.pre & PRE_GATES) && lane < n) {
@@ -1671,83 +1593,103 @@ __device__ __forceinline__ void chunk_terms_bf16(const Params& p, const long gi,
         }
         const double xn = __shfl(x, 63, 64);
         const float dec = __builtin_amdgcn_exp2f((float)(xn - x));
-        sGl[lane] = x;
-        sB[lane] = bv;
-        sD[lane] = dec;
-        if (store) {
-            const auto rg = rsrc(p.wsG + slot * GS, GS * 4);
-            bstore4<AUX>(__builtin_amdgcn_exp2f((float)x), rg, lane * 4);
-            bstore4<AUX>(dec, rg, (CH + lane) * 4);
-        }
+        lds.G[lane] = x;
+        lds.B[lane] = bv;
+        lds.D[lane] = dec;
+        const auto rg = rsrc(p.wsG + slot * GS, GS * 4);
+        bstore4<AUX>(__builtin_amdgcn_exp2f((float)x), rg, lane * 4);
+        bstore4<AUX>(dec, rg, (CH + lane) * 4);
     }
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-    __syncthreads();
     if constexpr (NORM) {
-        // reciprocal row lengths: 4 lanes per row, each summing 4 of its 16-byte pieces (in any order)
-        const int r = tid >> 2, part = tid & 3;
-        float sk = 0.f, sq = 0.f;
+        // reciprocal row lengths: a lane holds a quarter of row 16 rb + l16
 #pragma unroll
-        for (int j = 0; j < NCH / 4; ++j) {
-            const bf16x8 a = *reinterpret_cast<const bf16x8*>(sK + r * DK + 8 * (NCH / 4 * part + j));
-            const bf16x8 b = *reinterpret_cast<const bf16x8*>(sQ + r * DK + 8 * (NCH / 4 * part + j));
+        for (int rb = 0; rb < 4; ++rb) {
+            float sk = 0.f, sq = 0.f;
 #pragma unroll
-            for (int e = 0; e < 8; ++e) {
-                sk += (float)a[e] * (float)a[e];
-                sq += (float)b[e] * (float)b[e];
+            for (int kk = 0; kk < NKD; ++kk)
+#pragma unroll
+                for (int e = 0; e < 8; ++e) {
+                    sk += (float)kf[rb][kk][e] * (float)kf[rb][kk][e];
+                    sq += (float)qf[rb][kk][e] * (float)qf[rb][kk][e];
+                }
+            sk += __shfl_xor(sk, 16, 64);
+            sk += __shfl_xor(sk, 32, 64);
+            sq += __shfl_xor(sq, 16, 64);
+            sq += __shfl_xor(sq, 32, 64);
+            if (lg == 0) {
+                const int r = 16 * rb + l16;
+                lds.Sk[r] = r < n ? 1.f / sqrtf(sk + L2_EPS) : 0.f;
+                lds.Sq[r] = r < n ? 1.f / sqrtf(sq + L2_EPS) : 0.f;
             }
         }
-        sk += __shfl_xor(sk, 1, 64);
-        sk += __shfl_xor(sk, 2, 64);
-        sq += __shfl_xor(sq, 1, 64);
-        sq += __shfl_xor(sq, 2, 64);
-        if (part == 0) {
-            sSk[r] = r < n ? 1.f / sqrtf(sk + L2_EPS) : 0.f;
-            sSq[r] = r < n ? 1.f / sqrtf(sq + L2_EPS) : 0.f;
-        }
-        __syncthreads();
-        if (store && tid < CH) {   // the chain's decays for K S^T and Q S^T: gamma s_k, gamma s_q
-            const auto rg = rsrc(p.wsG + slot * GS, GS * 4);
-            const float gam = __builtin_amdgcn_exp2f((float)sGl[tid]);
-            bstore4<AUX>(gam * sSk[tid], rg, (2 * CH + tid) * 4);
-            bstore4<AUX>(gam * sSq[tid], rg, (3 * CH + tid) * 4);
-        }
+        wave_lds_fence();
+        // the chain's decays for K S^T and Q S^T: gamma s_k, gamma s_q
+        const auto rg = rsrc(p.wsG + slot * GS, GS * 4);
+        const float gam = __builtin_amdgcn_exp2f((float)lds.G[lane]);
+        bstore4<AUX>(gam * lds.Sk[lane], rg, (2 * CH + lane) * 4);
+        bstore4<AUX>(gam * lds.Sq[lane], rg, (3 * CH + lane) * 4);
     }
-    if constexpr (FUSED) {   // V rows of the item into L2 (waited for before the flag is set)
-        const int DV = p.DV, vch = DV / 8, vrpi = 64 / vch;
-        const auto rv = rsrc(reinterpret_cast<const bf16_t*>(p.v) + (t0 * H + h) * DV,
-                             (uint32_t)(((long)(n - 1) * H + 1) * DV * 2));
-        for (int i = wave; i < CH / vrpi; i += 4)
-            bdma16(rv, vsink + i * 512, ((vrpi * i + lane / vch) * H * DV + (lane % vch) * 8) * 2);
-    }
+    wave_lds_fence();
 
-    // token-token blocks, all operands in registers
-    floatx4 ablk[3], pblk[3];
-    switch (wave) {
-        case 0: gram_blocks<DK, 0, NORM>(sK, sQ, sGl, sB, sSk, sSq, l16, lg, ablk, pblk); break;
-        case 1: gram_blocks<DK, 1, NORM>(sK, sQ, sGl, sB, sSk, sSq, l16, lg, ablk, pblk); break;
-        case 2: gram_blocks<DK, 2, NORM>(sK, sQ, sGl, sB, sSk, sSq, l16, lg, ablk, pblk); break;
-        default: gram_blocks<DK, 3, NORM>(sK, sQ, sGl, sB, sSk, sSq, l16, lg, ablk, pblk); break;
+    // token-token blocks: ab = A_mj below the diagonal blocks, pk[m][b] = P_bm^T
+    floatx4 ab[4][4];   // [m][j], j < m
+    bf16x4 pk[4][4];    // [m][b], m <= b
+    double gc16[4];     // G of row 16 j + l16
+#pragma unroll
+    for (int j = 0; j < 4; ++j) gc16[j] = lds.G[16 * j + l16];
+#pragma unroll
+    for (int m = 0; m < 4; ++m) {
+        double gr[4];
+        float br[4], sr[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            gr[e] = lds.G[16 * m + 4 * lg + e];
+            br[e] = lds.B[16 * m + 4 * lg + e];
+            sr[e] = NORM ? lds.Sk[16 * m + 4 * lg + e] : 1.f;
+        }
+#pragma unroll
+        for (int j = 0; j <= m; ++j) {
+            floatx4 acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int kk = 0; kk < NKD; ++kk) acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf[m][kk], kf[j][kk], acc, 0, 0, 0);
+            const float sc = NORM ? lds.Sk[16 * j + l16] : 1.f;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const float gam = __builtin_amdgcn_exp2f((float)(gr[e] - gc16[j]));
+                if constexpr (NORM) acc[e] *= sr[e] * sc;
+                acc[e] = j < m || 4 * lg + e > l16 ? br[e] * gam * acc[e] : 0.f;
+            }
+            if (j == m) {
+#pragma unroll
+                for (int e = 0; e < 4; ++e) lds.X[m][4 * lg + e][l16] = acc[e];
+            } else {
+                ab[m][j] = acc;
+            }
+        }
+#pragma unroll
+        for (int b = m; b < 4; ++b) {
+            floatx4 acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int kk = 0; kk < NKD; ++kk) acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf[m][kk], qf[b][kk], acc, 0, 0, 0);
+            const float sc = NORM ? lds.Sq[16 * b + l16] : 1.f;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const float gam = __builtin_amdgcn_exp2f((float)(gc16[b] - gr[e]));
+                if constexpr (NORM) acc[e] *= sr[e] * sc;
+                acc[e] = m < b || l16 >= 4 * lg + e ? gam * acc[e] : 0.f;
+            }
+            pk[m][b] = __builtin_convertvector(acc, bf16x4);
+        }
     }
-    __syncthreads();   // every tile read done: A, P and T take the space over
-    switch (wave) {
-        case 0: store_gram<DK, 0>(sA, sPb, l16, lg, ablk, pblk); break;
-        case 1: store_gram<DK, 1>(sA, sPb, l16, lg, ablk, pblk); break;
-        case 2: store_gram<DK, 2>(sA, sPb, l16, lg, ablk, pblk); break;
-        default: store_gram<DK, 3>(sA, sPb, l16, lg, ablk, pblk); break;
-    }
-    __syncthreads();
+    wave_lds_fence();
 
-    // T = (I + A)^{-1}: diagonal blocks by forward substitution, one wave, lane =
-    // 16 * block + column, A's block rows in registers.  The upper blocks of P
-    // and T are never stored: their readers take them as zero.
-    if (wave == 0) {
-        const int b = lg;
+    {   // diagonal blocks of T by forward substitution: lane = 16 * block + column
         float a[16][16];
 #pragma unroll
         for (int r = 1; r < 16; ++r)
 #pragma unroll
             for (int q = 0; 4 * q < r; ++q) {
-                const floatx4 v = *reinterpret_cast<const floatx4*>(&sA[16 * b + r][16 * b + 4 * q]);
+                const floatx4 v = *reinterpret_cast<const floatx4*>(&lds.X[lg][r][4 * q]);
 #pragma unroll
                 for (int t = 0; t < 4; ++t) a[r][4 * q + t] = v[t];
             }
@@ -1758,103 +1700,127 @@ __device__ __forceinline__ void chunk_terms_bf16(const Params& p, const long gi,
         for (int i = 0; i < 15; ++i)
 #pragma unroll
             for (int r = i + 1; r < 16; ++r) x[r] -= a[r][i] * x[i];
+        wave_lds_fence();
 #pragma unroll
-        for (int r = 0; r < 16; ++r) sTi[16 * b + r][16 * b + l16] = x[r];
+        for (int r = 0; r < 16; ++r) lds.X[lg][r][l16] = x[r];
     }
-    __syncthreads();
-    // off-diagonal blocks, diagonal d: T_{b,b-d} = -T_bb sum_{m} A_bm T_{m,b-d}.
-    // In MFMA step kk, lane group lg carries contraction index 4 lg + kk, so the
-    // sum Z comes out of the accumulator exactly as the second product's B operand.
-    for (int d = 1; d < 4; ++d) {
-        if (wave < 4 - d) {
-            const int j = wave, b = wave + d;
-            floatx4 z = {0.f, 0.f, 0.f, 0.f};
-            for (int m = j; m < b; ++m) {
-                const floatx4 av = *reinterpret_cast<const floatx4*>(&sA[16 * b + l16][16 * m + 4 * lg]);
+    wave_lds_fence();
+    floatx4 y[4][4];   // [j][b], j <= b: T_bj^T
+    floatx4 td[4];     // T_jj, D layout
 #pragma unroll
-                for (int kk = 0; kk < 4; ++kk)
-                    z = __builtin_amdgcn_mfma_f32_16x16x4f32(av[kk], sTi[16 * m + 4 * lg + kk][16 * j + l16], z, 0, 0, 0);
-            }
-            const floatx4 tv = *reinterpret_cast<const floatx4*>(&sTi[16 * b + l16][16 * b + 4 * lg]);
-            floatx4 t = {0.f, 0.f, 0.f, 0.f};
+    for (int j = 0; j < 4; ++j) {
+        y[j][j] = *reinterpret_cast<const floatx4*>(&lds.X[j][l16][4 * lg]);
 #pragma unroll
-            for (int kk = 0; kk < 4; ++kk) t = __builtin_amdgcn_mfma_f32_16x16x4f32(tv[kk], z[kk], t, 0, 0, 0);
+        for (int e = 0; e < 4; ++e) td[j][e] = lds.X[j][4 * lg + e][l16];
+    }
 #pragma unroll
-            for (int e = 0; e < 4; ++e) sTi[16 * b + 4 * lg + e][16 * j + l16] = -t[e];
+    for (int d = 1; d < 4; ++d)
+#pragma unroll
+        for (int j = 0; j < 4 - d; ++j) {
+            const int b = j + d;
+            floatx4 z = {0.f, 0.f, 0.f, 0.f}, t = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int m = j + 1; m <= b; ++m)
+#pragma unroll
+                for (int kk = 0; kk < 4; ++kk) z = __builtin_amdgcn_mfma_f32_16x16x4f32(ab[m][j][kk], y[m][b][kk], z, 0, 0, 0);
+#pragma unroll
+            for (int kk = 0; kk < 4; ++kk) t = __builtin_amdgcn_mfma_f32_16x16x4f32(td[j][kk], z[kk], t, 0, 0, 0);
+            y[j][b] = -t;
         }
-        __syncthreads();
-    }
-    for (int i = tid; i < CH * CH / 4; i += NT) {   // bf16 copy of T, zero above the diagonal blocks (A is no longer read)
-        const int r = i / (CH / 4), c4 = 4 * (i % (CH / 4));
-        floatx4 v = *reinterpret_cast<const floatx4*>(&sTi[r][c4]);
-        if ((c4 >> 4) > (r >> 4)) v = floatx4{0.f, 0.f, 0.f, 0.f};
-        *reinterpret_cast<bf16x4*>(&sTb[r][c4]) = __builtin_convertvector(v, bf16x4);
-    }
-    __syncthreads();
+#pragma unroll
+    for (int b = 0; b < 4; ++b)
+#pragma unroll
+        for (int j = 0; j <= b; ++j)
+            *reinterpret_cast<bf16x4*>(&lds.Tb[16 * b + l16][16 * j + 4 * lg]) = __builtin_convertvector(y[j][b], bf16x4);
+    wave_lds_fence();
 
     const auto rW = rsrc(reinterpret_cast<bf16_t*>(p.wsT) + slot * tp_elems<bf16_t>(), tp_elems<bf16_t>() * 2);
     const auto rP = rsrc(reinterpret_cast<bf16_t*>(p.wsP) + slot * tp_elems<bf16_t>(), tp_elems<bf16_t>() * 2);
-    for (int f = wave; f < NFRAG; f += 4) {
-        const int mt = frag_mt(f), kk2 = frag_kk(f), r = 16 * mt + l16;
-        // W fragment: D_r T[r][tau] beta_tau (times s_k,r with PRE_L2: the state update takes K unscaled)
-        const float dr = NORM ? sD[r] * sSk[r] : sD[r];
-        const floatx4 b0 = *reinterpret_cast<const floatx4*>(&sB[32 * kk2 + 4 * lg]);
-        const floatx4 b1 = *reinterpret_cast<const floatx4*>(&sB[32 * kk2 + 16 + 4 * lg]);
-        const floatx4 zero = {0.f, 0.f, 0.f, 0.f};   // blocks of T above the diagonal
-        const floatx4 w0 = 2 * kk2 > mt ? zero : dr * b0 * *reinterpret_cast<const floatx4*>(&sTi[r][32 * kk2 + 4 * lg]);
-        const floatx4 w1 =
-            2 * kk2 + 1 > mt ? zero : dr * b1 * *reinterpret_cast<const floatx4*>(&sTi[r][32 * kk2 + 16 + 4 * lg]);
-        if (store) bstore16<AUX>(pack_bf16(w0, w1), rW, (f * 64 + lane) * 16);
-        // P' fragment from (T^T P^T) tiles (tau block 2 kk2 + hb, token block mt)
-        floatx4 pt[2];
+    floatx4 bt4[4];   // beta of tokens 16 j + 4 lg + e
 #pragma unroll
-        for (int hb = 0; hb < 2; ++hb) {
-            const int bt = 2 * kk2 + hb;
-            pt[hb] = floatx4{0.f, 0.f, 0.f, 0.f};
-            if (bt > mt) continue;   // above the diagonal: zero
+    for (int j = 0; j < 4; ++j) bt4[j] = *reinterpret_cast<const floatx4*>(&lds.B[16 * j + 4 * lg]);
+    const floatx4 zero = {0.f, 0.f, 0.f, 0.f};
+    const short4v zero4 = {0, 0, 0, 0};
+    bf16x8 tf[4][2];   // T^T operands: row 16 j + l16, tokens 32 kk + 16 (i / 4) + 4 lg + i % 4
 #pragma unroll
-            for (int kk = 0; kk < 2; ++kk) {
-                const bf16_t* t0p = &sTb[32 * kk + 8 * lg + (l16 >> 2)][16 * bt + 4 * (l16 & 3)];
-                const bf16x8 a = join4(lds_tr8(t0p), lds_tr8(t0p + 4 * PB));
-                bf16x8 bb = *reinterpret_cast<const bf16x8*>(&sPb[16 * mt + l16][32 * kk + 8 * lg]);
-                if (2 * kk + (lg >> 1) > mt) bb = bf16x8{};   // blocks of P above the diagonal
-                pt[hb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, bb, pt[hb], 0, 0, 0);
-            }
-            pt[hb] *= hb ? b1 : b0;
+    for (int j = 0; j < 4; ++j)
+#pragma unroll
+        for (int kk = j / 2; kk < 2; ++kk) {
+            const bf16_t* at = &lds.Tb[32 * kk + 4 * lg + (l16 >> 2)][16 * j + 4 * (l16 & 3)];
+            tf[j][kk] = join4(2 * kk >= j ? lds_tr8(at) : zero4, lds_tr8(at + 16 * (CH + 8)));
         }
-        if (store) bstore16<AUX>(pack_bf16(pt[0], pt[1]), rP, (f * 64 + lane) * 16);
+#pragma unroll
+    for (int mt = 0; mt < 4; ++mt) {
+        // W: D_r T[r][tau] beta_tau (times s_k,r with PRE_L2: the state update takes K unscaled)
+        const float dr = NORM ? lds.D[16 * mt + l16] * lds.Sk[16 * mt + l16] : lds.D[16 * mt + l16];
+        bf16x8 pb[2];   // P^T of token tile mt
+#pragma unroll
+        for (int kk = 0; kk <= mt / 2; ++kk)
+            pb[kk] = join4(__builtin_bit_cast(short4v, pk[2 * kk][mt]),
+                           2 * kk + 1 <= mt ? __builtin_bit_cast(short4v, pk[2 * kk + 1][mt]) : zero4);
+#pragma unroll
+        for (int kk2 = 0; kk2 <= mt / 2; ++kk2) {
+            const int f = frag_id(mt, kk2);
+            floatx4 w[2], pt[2];
+#pragma unroll
+            for (int hb = 0; hb < 2; ++hb) {
+                const int j = 2 * kk2 + hb;
+                w[hb] = pt[hb] = zero;
+                if (j > mt) continue;   // above the diagonal
+                w[hb] = dr * bt4[j] * y[j][mt];
+#pragma unroll
+                for (int kk = j / 2; kk <= mt / 2; ++kk)
+                    pt[hb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(tf[j][kk], pb[kk], pt[hb], 0, 0, 0);
+                pt[hb] *= bt4[j];
+            }
+            bstore16<AUX>(pack_bf16(w[0], w[1]), rW, (f * 64 + lane) * 16);
+            bstore16<AUX>(pack_bf16(pt[0], pt[1]), rP, (f * 64 + lane) * 16);
+        }
     }
-    if constexpr (FUSED) {   // publish: every wave's stores are complete before the flag is set
+    if constexpr (FUSED) {   // publish: every store is complete before the flag is set
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-        __syncthreads();
-        if (tid == 0 && store && !p.withhold)   // (relaxed: see the flag poller of state_chain_bf16)
+        if (lane == 0 && !p.withhold)   // (relaxed: see the flag poller of state_chain_bf16)
             __hip_atomic_store(&p.flags[slot], p.epoch, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+        const int DV = p.DV, vch = DV / 8, vrpi = 64 / vch;   // V rows of the item into L2
+        const auto rv = rsrc(reinterpret_cast<const bf16_t*>(p.v) + (t0 * H + h) * DV,
+                             (uint32_t)(((long)(n - 1) * H + 1) * DV * 2));
+        for (int i = 0; i < CH / vrpi; ++i)
+            bdma16(rv, vsink, ((vrpi * i + lane / vch) * H * DV + (lane % vch) * 8) * 2);
     }
 }
 
+// One wave per workgroup: two waves per SIMD (their registers hold a chunk's K and Q).
 template <int DK, bool NORM = false>
-__global__ __launch_bounds__(NT, 3) void k_chunk_terms_bf16(Params p) {
-    __shared__ TermsLds<DK> lds;
-    chunk_terms_bf16<DK, false, NORM>(p, blockIdx.x, lds, threadIdx.x, true);
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_chunk_terms_bf16(Params p) {
+    __shared__ TermsLds lds;
+    chunk_terms_bf16<DK, false, NORM>(p, blockIdx.x, lds, threadIdx.x);
 }
 
 // One launch for the whole bf16 prefill: workgroups [0, npw) form chunk terms
-// (two work items per workgroup, one per half of its waves, walking the items
-// in chunk order), the rest are chain workgroups.  The chunk-terms workgroups
-// are dispatched first and never wait, so the chain workgroups' waits end
-// whatever number of workgroups the device holds at once.
+// (one work item per wave at a time, walking the items in chunk order, first
+// the first wave of every workgroup), the rest are chain workgroups.  The
+// chunk-terms workgroups are dispatched first and never wait, so the chain
+// workgroups' waits end whatever number of workgroups the device holds at once.
+// Two waves form chunk terms in each such workgroup: enough to stay ahead of the
+// chain (16 heads consume 16 items per 0.74 us; an item takes about 9 us, 256 at
+// once).  More waves run further ahead than the L2s hold, so the chain finds its K,
+// Q and V rows gone from them, and crowd its loads: with 1, 2, 3, 4 and 8 waves the
+// call of 10240 tokens and 16 heads took 160, 131.7, 140, 145 and 154 us.
+constexpr int TERM_WAVES = 2;
 template <int DK, bool SNAP = false, bool NORM = false>
 __global__ __launch_bounds__(NT_CHAIN) __attribute__((amdgpu_waves_per_eu(1, 2))) void k_prefill_fused_bf16(Params p) {
-    static_assert(NT_CHAIN == 2 * NT, "two work items per chunk-terms workgroup");
     __shared__ union Lds {
+        __device__ Lds() {}
         ChainLds<DK> c;
         struct {
-            TermsLds<DK> t;
-            bf16_t vsink[CH * 128];
-        } t[2];
+            TermsLds t;
+            bf16_t vsink[512];
+        } t[TERM_WAVES];
     } lds;
     if ((int)blockIdx.x < p.npw) {
-        const int half = __builtin_amdgcn_readfirstlane(threadIdx.x / NT);   // wave-uniform
+        const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+        if (wave >= TERM_WAVES) return;
+        auto& my = lds.t[wave];
         if (p.xcd_items) {
             // Dispatch deals workgroups to the 8 XCDs round-robin, so chain
             // workgroups of head h sit on XCD (npw + h) % 8.  Workgroup b forms
@@ -1863,23 +1829,16 @@ __global__ __launch_bounds__(NT_CHAIN) __attribute__((amdgpu_waves_per_eu(1, 2))
             const int H = p.H, hu = H / 8, q = blockIdx.x / 8, nq = p.npw / 8;
             const int h0 = ((int)(blockIdx.x % 8) - p.npw % 8 + 8) % 8;
             const long items = (long)p.NC * p.n_seq * hu;   // per XCD
-            for (long k = 2L * q; k < items; k += 2L * nq) {
-                const long j = min(k + half, items - 1);
+            for (long j = (long)wave * nq + q; j < items; j += (long)TERM_WAVES * nq) {
                 const int c = (int)(j / ((long)p.n_seq * hu)), r = (int)((j / hu) % p.n_seq), u = (int)(j % hu);
-                const long gi = ((long)r * p.NC + c) * H + h0 + 8 * u;
-                chunk_terms_bf16<DK, true, NORM>(p, gi, lds.t[half].t, threadIdx.x % NT, k + half < items,
-                                                 lds.t[half].vsink);
-                __syncthreads();   // the next item reuses the LDS
+                chunk_terms_bf16<DK, true, NORM>(p, ((long)r * p.NC + c) * H + h0 + 8 * u, my.t, lane, my.vsink);
             }
         } else {
             const long items = (long)(p.ragged ? tab(p.chunk_off, p.n_seq) : p.n_seq * p.NC) * p.H;
-            for (long k = 2L * blockIdx.x; k < items; k += 2L * p.npw) {
-                const long gi = item_slot(p, min(k + half, items - 1));   // both halves run every step together
-                chunk_terms_bf16<DK, true, NORM>(p, gi, lds.t[half].t, threadIdx.x % NT, k + half < items,
-                                                 lds.t[half].vsink);
-                __syncthreads();   // the next item reuses the LDS
-            }
+            for (long k = (long)wave * p.npw + blockIdx.x; k < items; k += (long)TERM_WAVES * p.npw)
+                chunk_terms_bf16<DK, true, NORM>(p, item_slot(p, k), my.t, lane, my.vsink);
         }
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // the copies into vsink
     } else {
         state_chain_bf16<DK, true, false, SNAP, NORM>(p, blockIdx.x - p.npw, lds.c);
     }
@@ -2655,7 +2614,7 @@ void launch_prefill(Params p, long slots, hipStream_t st) {
         const long cus = stream_cus(st);
         const long spare = cus - nchain;   // CUs the chain leaves free (one chain workgroup per CU)
         if (spare >= 8 && 4 * spare >= cus && items > 0) {
-            p.npw = (int)std::min(spare, (items + 1) / 2);
+            p.npw = (int)std::min(spare, (items + TERM_WAVES - 1) / TERM_WAVES);
             p.xcd_items = !p.ragged && p.H % 8 == 0 && p.npw >= 8;
             if (p.xcd_items) p.npw &= ~7;
             p.epoch = next_epoch();
@@ -2666,7 +2625,7 @@ void launch_prefill(Params p, long slots, hipStream_t st) {
     }
     if (slots > 0 && p.T > 0) {
         if constexpr (sizeof(IO) == 2)
-            hipLaunchKernelGGL((k_chunk_terms_bf16<DK, NORM>), dim3((unsigned)(slots * p.H)), dim3(NT), 0, st, p);
+            hipLaunchKernelGGL((k_chunk_terms_bf16<DK, NORM>), dim3((unsigned)(slots * p.H)), dim3(64), 0, st, p);
         else
             hipLaunchKernelGGL((k_chunk_terms<DK>), dim3((unsigned)(slots * p.H)), dim3(NT_T32), 0, st, p);
     }
@@ -2842,7 +2801,7 @@ void launch_segmented(Params p, const SegParams& sq, long slots, hipStream_t st)
     hipLaunchKernelGGL((k_segment_prep<DK>), dim3((unsigned)((per_seg + NT - 1) / NT), (unsigned)(nseg + 1)), dim3(NT), 0,
                        st, sq);
     if constexpr (sizeof(IO) == 2)
-        hipLaunchKernelGGL((k_chunk_terms_bf16<DK, NORM>), dim3((unsigned)(slots * p.H)), dim3(NT), 0, st, p);
+        hipLaunchKernelGGL((k_chunk_terms_bf16<DK, NORM>), dim3((unsigned)(slots * p.H)), dim3(64), 0, st, p);
     else
         hipLaunchKernelGGL((k_chunk_terms<DK>), dim3((unsigned)(slots * p.H)), dim3(NT_T32), 0, st, p);
     ChainAlt a;
@@ -2865,7 +2824,7 @@ void launch_segmented(Params p, const SegParams& sq, long slots, hipStream_t st)
 template <int DK>
 void launch_wide(Params p, WideParams w, hipStream_t st) {
     const long BH = (long)w.B * w.H;
-    hipLaunchKernelGGL((k_chunk_terms_bf16<DK, false>), dim3((unsigned)(BH * w.NC)), dim3(NT), 0, st, p);
+    hipLaunchKernelGGL((k_chunk_terms_bf16<DK, false>), dim3((unsigned)(BH * w.NC)), dim3(64), 0, st, p);
     hipLaunchKernelGGL((k_wide_states<DK>), dim3((unsigned)(BH * (w.P - 1))), dim3(4 * DK), 0, st, w);
     hipLaunchKernelGGL((k_wide_scan<DK>), dim3((unsigned)(8 * ((BH + 7) / 8) * (w.D / 16))), dim3(DK * 4), 0, st, w);
     hipLaunchKernelGGL((k_wide_out<DK>), dim3((unsigned)(BH * w.P)), dim3(4 * DK), 0, st, w);
