@@ -310,7 +310,6 @@ typedef short short4v __attribute__((ext_vector_type(4)));
 typedef int int4v __attribute__((ext_vector_type(4)));
 typedef __attribute__((address_space(3))) void lds_void;
 constexpr int NT_CHAIN = 512;
-constexpr int RING = 4;
 template <int N> struct Ic { static constexpr int value = N; };
 
 __device__ __forceinline__ bf16x8 pack_bf16(floatx4 a, floatx4 b) {
@@ -968,19 +967,25 @@ __global__ __launch_bounds__(NT_CHAIN) __attribute__((amdgpu_waves_per_eu(1, 2))
 // in flight across them.
 // The chunk loop is unrolled by the ring depth so ring slots are constants.
 
+// Row groups (NR) of 16 state rows per chain workgroup: with two, every K, W, Q and P'
+// operand that a workgroup loads serves 32 rows, but a chunk step is longer; LDS then holds
+// a ring of three chunks instead of four.
+constexpr int chain_ring(int nr) { return nr == 1 ? 4 : 3; }
+
 // LDS of one chain workgroup
-template <int DK> struct ChainLds {
-    bf16_t sK[RING][CH * DK];     // ring of chunk inputs (slot = chunk % RING)
-    bf16x8 sW[RING][NFRAG][64];   // diag(D) T diag(beta)
-    bf16_t sV[RING][CH * SL];
-    float sG[RING][CH];           // gamma_r
-    float sGk[RING][CH];          // gamma_r s_k,r and gamma_r s_q,r (PRE_L2: K and Q taken unscaled)
-    float sGq[RING][CH];
-    bf16x8 sSf[2][DK / 32][64];   // S_c and R'_c as MFMA operands, by chunk parity
-    bf16x8 sRf[2][2][64];
-    floatx4 sY[2][2][64];         // each chain wave's share of X_{c+1} for the other wave's token tiles
-    bf16_t sQ[2][2][32 * DK];     // Q rows of each output wave, by chunk parity
-    int failed;                   // one launch: a wait for chunk terms gave up (set by the flag poller)
+template <int DK, int NR> struct ChainLds {
+    static constexpr int RD = chain_ring(NR);
+    bf16_t sK[RD][CH * DK];            // ring of chunk inputs (slot = chunk % RD)
+    bf16x8 sW[RD][NFRAG][64];          // diag(D) T diag(beta)
+    bf16_t sV[RD][NR][CH * SL];
+    float sG[RD][CH];                  // gamma_r
+    float sGk[RD][CH];                 // gamma_r s_k,r and gamma_r s_q,r (PRE_L2: K and Q taken unscaled)
+    float sGq[RD][CH];
+    bf16x8 sSf[2][NR][DK / 32][64];    // S_c and R'_c as MFMA operands, by chunk parity
+    bf16x8 sRf[2][NR][2][64];
+    floatx4 sY[NR][2][2][64];          // each chain wave's share of X_{c+1} for the other wave's token tiles
+    bf16_t sQ[2][2][32 * DK];          // Q rows of each output wave, by chunk parity
+    int failed;                        // one launch: a wait for chunk terms gave up (set by the flag poller)
 };
 
 // Chain workgroup `bid`.  FUSED: the chunk terms come from workgroups of the
@@ -991,8 +996,10 @@ template <int DK> struct ChainLds {
 // state is also stored after every snap_every chunks.  NORM (PRE_L2): K and Q
 // rows arrive unscaled, so K S^T and Q S^T take the decays gamma s_k and gamma
 // s_q (the chunk terms fold s_k into W).
-template <int DK, bool FUSED, bool IDENT = false, bool SNAP = false, bool NORM = false>
-__device__ __forceinline__ void state_chain_bf16(const Params& p, const int bid, ChainLds<DK>& lds) {
+template <int DK, int NR, bool FUSED, bool IDENT = false, bool SNAP = false, bool NORM = false>
+__device__ __forceinline__ void state_chain_bf16(const Params& p, const int bid, ChainLds<DK, NR>& lds) {
+    constexpr int RD = chain_ring(NR), ROWS = SL * NR;
+    constexpr int UN = RD % 2 ? 2 * RD : RD;   // chunk steps the loops unroll: ring slot and parity are constants
     constexpr int NKD = DK / 32;        // MFMA contraction blocks over the key channels
     constexpr int HKD = NKD / 2;        // ... whose S^T rows one chain wave keeps
     constexpr int HMD = DK / 32;        // 16-row S^T tiles per chain wave
@@ -1003,7 +1010,7 @@ __device__ __forceinline__ void state_chain_bf16(const Params& p, const int bid,
     // slice-major, so the slices of one (sequence, head) are congruent modulo H:
     // with 8 | H they share an XCD (dispatch is round-robin over the 8 XCDs) and
     // its L2 copy of K, Q and the chunk matrices.
-    const int per = H * (DV / SL);
+    const int per = H * (DV / ROWS);
     const int s = seq_at_rank(p, bid / per);
     const int js = (bid % per) / H;
     const int h = bid % H;
@@ -1025,7 +1032,7 @@ __device__ __forceinline__ void state_chain_bf16(const Params& p, const int bid,
 
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int l16 = lane & 15, lg = lane >> 4;
-    const long srow0 = ((long)(s * H + h) * DV + js * SL) * DK;
+    const long srow0 = ((long)(s * H + h) * DV + js * ROWS) * DK;
     auto rows = [&](int c) { return min(CH, len - c * CH); };
     auto tok0 = [&](int c) { return start + (long)c * CH; };
     auto slot = [&](int c) { return (long)(cbase + c) * H + h; };
@@ -1042,6 +1049,19 @@ __device__ __forceinline__ void state_chain_bf16(const Params& p, const int bid,
     auto krsrc = [&](const void* base, int c) {
         return rsrc(reinterpret_cast<const bf16_t*>(base) + (tok0(c) * HK + hk) * DK,
                     (uint32_t)(((long)(rows(c) - 1) * HK + 1) * DK * 2));
+    };
+    // the chunk loop of a role, unrolled so that ring slots and parity are constants: step(c, c mod UN)
+    auto chunks = [&](auto& step) {
+        for (int c = 0; c < nc; c += UN) {
+            step(c, Ic<0>{});
+            if (c + 1 < nc) step(c + 1, Ic<1>{});
+            if (c + 2 < nc) step(c + 2, Ic<2>{});
+            if (c + 3 < nc) step(c + 3, Ic<3>{});
+            if constexpr (UN > 4) {
+                if (c + 4 < nc) step(c + 4, Ic<4>{});
+                if (c + 5 < nc) step(c + 5, Ic<5>{});
+            }
+        }
     };
     // values; the identity run's read as zeros (a descriptor of no bytes)
     auto vrsrc = [&](int c) { return IDENT ? rsrc(p.k, 0u) : crsrc(p.v, DV, c); };
@@ -1110,14 +1130,16 @@ __device__ __forceinline__ void state_chain_bf16(const Params& p, const int bid,
             const int r = RPI * (li + NL * j) + lane / NCH;
             koff[j] = (r * HK * DK + (((lane % NCH) ^ swz(r)) << 3)) * 2;
         }
-        const int voff = ((32 * (li == NL - 1) + (lane >> 1)) * H * DV + js * SL + (lane & 1) * 8) * 2;
+        const int voff = ((32 * (li == NL - 1) + (lane >> 1)) * H * DV + js * ROWS + (lane & 1) * 8) * 2;
         // a chunk's copies of the inputs (K, V) and of its chunk terms (W, gamma)
         auto issue_in = [&](int c, auto SLOT, auto LI) {
             constexpr int sl = decltype(SLOT)::value, L = decltype(LI)::value;
             const auto rk = krsrc(p.k, c);
 #pragma unroll
             for (int i = L; i < NCH; i += NL) bdma16(rk, &sK[sl][RPI * i * DK], koff[i / NL]);
-            if constexpr (L >= NL - 2) bdma16(vrsrc(c), &sV[sl][32 * (L == NL - 1) * SL], voff);
+            if constexpr (L >= NL - 2)
+#pragma unroll
+                for (int nr = 0; nr < NR; ++nr) bdma16(vrsrc(c), &sV[sl][nr][32 * (L == NL - 1) * SL], voff + 2 * SL * nr);
         };
         auto issue_terms = [&](int c, auto SLOT, auto LI) {
             constexpr int sl = decltype(SLOT)::value, L = decltype(LI)::value;
@@ -1135,39 +1157,34 @@ __device__ __forceinline__ void state_chain_bf16(const Params& p, const int bid,
             issue_terms(c, SLOT, LI);
         };
         // After barrier A_c every wave is done with chunk c-1, whose slot is
-        // (c+3) % RING: chunk c+3 is loaded there, and the wait leaves only
-        // those loads in flight, so chunk c+2 has landed before barrier A_{c+1}.
+        // (c-1) % RD: chunk c+RD-1 is loaded there.  Step c+1 reads chunk c+2: with four
+        // slots the wait leaves the loads of this step in flight, with three it leaves none.
         auto run = [&](auto LI) {
             constexpr int L = decltype(LI)::value;
-            constexpr int NI = (NCH - L + NL - 1) / NL + (NFRAG - L + NL - 1) / NL + (L >= NL - 2) + (L == 0) +
+            constexpr int NI = (NCH - L + NL - 1) / NL + (NFRAG - L + NL - 1) / NL + NR * (L >= NL - 2) + (L == 0) +
                                (NORM && (L == 1 || L == 2));
             auto lstep = [&](int c, auto SLOT) {
-                constexpr int bn = (decltype(SLOT)::value + 3) % RING;
+                constexpr int bn = (decltype(SLOT)::value + RD - 1) % RD;
                 lds_barrier();   // A_c
-                issue(min(c + 3, nc - 1), Ic<bn>{}, LI);
+                issue(min(c + RD - 1, nc - 1), Ic<bn>{}, LI);
                 lds_barrier();   // B_c
-                asm volatile("s_waitcnt vmcnt(%0)" ::"n"(NI) : "memory");
+                asm volatile("s_waitcnt vmcnt(%0)" ::"n"(NI * (RD - 3)) : "memory");
             };
             if (nc > 0) {   // the inputs need no chunk terms: copied while those are formed
                 issue_in(0, Ic<0>{}, LI);
                 issue_in(min(1, nc - 1), Ic<1>{}, LI);
-                issue_in(min(2, nc - 1), Ic<2>{}, LI);
+                if constexpr (RD > 3) issue_in(min(2, nc - 1), Ic<2>{}, LI);
             }
             lds_barrier();   // prologue P
             if (nc > 0) {
                 issue_terms(0, Ic<0>{}, LI);
                 issue_terms(min(1, nc - 1), Ic<1>{}, LI);
-                issue_terms(min(2, nc - 1), Ic<2>{}, LI);
+                if constexpr (RD > 3) issue_terms(min(2, nc - 1), Ic<2>{}, LI);
             }
             asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
             lds_barrier();   // prologue 1: chunks 0, 1 and 2 resident
             lds_barrier();   // prologue 2: S_0 halves visible
-            for (int c = 0; c < nc; c += RING) {
-                lstep(c, Ic<0>{});
-                if (c + 1 < nc) lstep(c + 1, Ic<1>{});
-                if (c + 2 < nc) lstep(c + 2, Ic<2>{});
-                if (c + 3 < nc) lstep(c + 3, Ic<3>{});
-            }
+            chunks(lstep);
             asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
         };
         switch (li) {
@@ -1184,12 +1201,15 @@ __device__ __forceinline__ void state_chain_bf16(const Params& p, const int bid,
         auto chain = [&](auto WI) {
             constexpr int w = decltype(WI)::value;
             auto chan = [&](int md) { return 32 * (md >> 1) + 8 * lg + 4 * (md & 1); };   // + e
-            floatx4 acc[HMD];
+            floatx4 acc[NR][HMD];
 #pragma unroll
-            for (int m = 0; m < HMD; ++m) {
-                acc[m] = floatx4{0.f, 0.f, 0.f, 0.f};
-                if (p.S0) acc[m] = *reinterpret_cast<const floatx4*>(p.S0 + srow0 + l16 * DK + chan(w * HMD + m));
-            }
+            for (int nr = 0; nr < NR; ++nr)
+#pragma unroll
+                for (int m = 0; m < HMD; ++m) {
+                    acc[nr][m] = floatx4{0.f, 0.f, 0.f, 0.f};
+                    if (p.S0)
+                        acc[nr][m] = *reinterpret_cast<const floatx4*>(p.S0 + srow0 + (SL * nr + l16) * DK + chan(w * HMD + m));
+                }
             // loop-invariant LDS offsets of this lane's operands
             int offT[HMD][2][2];      // K^T fragments of this wave's key tiles (transpose reads)
             int offV[2];              // V rows of this wave's token tiles (transpose reads)
@@ -1208,34 +1228,37 @@ __device__ __forceinline__ void state_chain_bf16(const Params& p, const int bid,
                         offT[m][kk][h2] = kq(32 * kk + 16 * h2 + 4 * lg + (l16 >> 2),
                                              32 * (md >> 1) + 8 * (l16 & 3) + 4 * (md & 1));
             }
-            bf16x8 sfo[HKD], rfo;   // this wave's halves of S_c and R'_c
+            bf16x8 sfo[NR][HKD], rfo[NR];   // this wave's halves of S_c and R'_c
             auto publish_s = [&](int par) {
 #pragma unroll
-                for (int k2 = 0; k2 < HKD; ++k2) {
-                    sfo[k2] = pack_bf16(acc[2 * k2], acc[2 * k2 + 1]);
-                    sSf[par][w * HKD + k2][lane] = sfo[k2];
-                }
+                for (int nr = 0; nr < NR; ++nr)
+#pragma unroll
+                    for (int k2 = 0; k2 < HKD; ++k2) {
+                        sfo[nr][k2] = pack_bf16(acc[nr][2 * k2], acc[nr][2 * k2 + 1]);
+                        sSf[par][nr][w * HKD + k2][lane] = sfo[nr][k2];
+                    }
             };
             // R' rows of this wave's token tiles from X = K S^T: V - diag(gamma) X
             struct VG {
-                short4v vv[2];
+                short4v vv[NR][2];
                 floatx4 gm[2];
             };
             auto load_vg = [&](int bn) {
                 VG r;
 #pragma unroll
                 for (int i = 0; i < 2; ++i) {
-                    r.vv[i] = lds_tr8(&sV[bn][offV[i]]);
+#pragma unroll
+                    for (int nr = 0; nr < NR; ++nr) r.vv[nr][i] = lds_tr8(&sV[bn][nr][offV[i]]);
                     r.gm[i] = *reinterpret_cast<const floatx4*>(&sGk[bn][16 * (2 * w + i) + 4 * lg]);
                 }
                 return r;
             };
-            auto rprime = [&](const floatx4 (&y)[2], const VG& vg) {
+            auto rprime = [&](const floatx4 (&y)[2], const VG& vg, int nr) {
                 floatx4 rr[2];
 #pragma unroll
                 for (int i = 0; i < 2; ++i)
 #pragma unroll
-                    for (int e = 0; e < 4; ++e) rr[i][e] = bf(vg.vv[i][e]) - vg.gm[i][e] * y[i][e];
+                    for (int e = 0; e < 4; ++e) rr[i][e] = bf(vg.vv[nr][i][e]) - vg.gm[i][e] * y[i][e];
                 return pack_bf16(rr[0], rr[1]);
             };
             lds_barrier();   // prologue P: chunks 0..2's terms published
@@ -1243,25 +1266,30 @@ __device__ __forceinline__ void state_chain_bf16(const Params& p, const int bid,
             if (nc > 0) publish_s(0);
             lds_barrier();   // prologue 2: S_0 halves visible
             if (nc > 0) {    // R'_0 = V_0 - diag(gamma_0) K_0 S_0^T for this wave's token tiles
-                bf16x8 sfx[HKD];
+                const VG vg = load_vg(0);
 #pragma unroll
-                for (int k2 = 0; k2 < HKD; ++k2) sfx[k2] = sSf[0][(1 - w) * HKD + k2][lane];
-                floatx4 y[2];
+                for (int nr = 0; nr < NR; ++nr) {
+                    bf16x8 sfx[HKD];
 #pragma unroll
-                for (int i = 0; i < 2; ++i) {
-                    y[i] = floatx4{0.f, 0.f, 0.f, 0.f};
+                    for (int k2 = 0; k2 < HKD; ++k2) sfx[k2] = sSf[0][nr][(1 - w) * HKD + k2][lane];
+                    floatx4 y[2];
 #pragma unroll
-                    for (int k2 = 0; k2 < HKD; ++k2) {
-                        const int r = 16 * (2 * w + i) + l16;
-                        y[i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
-                            *reinterpret_cast<const bf16x8*>(&sK[0][kq(r, 32 * (w * HKD + k2) + 8 * lg)]), sfo[k2], y[i], 0, 0, 0);
-                        y[i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
-                            *reinterpret_cast<const bf16x8*>(&sK[0][kq(r, 32 * ((1 - w) * HKD + k2) + 8 * lg)]), sfx[k2], y[i],
-                            0, 0, 0);
+                    for (int i = 0; i < 2; ++i) {
+                        y[i] = floatx4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                        for (int k2 = 0; k2 < HKD; ++k2) {
+                            const int r = 16 * (2 * w + i) + l16;
+                            y[i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+                                *reinterpret_cast<const bf16x8*>(&sK[0][kq(r, 32 * (w * HKD + k2) + 8 * lg)]), sfo[nr][k2], y[i],
+                                0, 0, 0);
+                            y[i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+                                *reinterpret_cast<const bf16x8*>(&sK[0][kq(r, 32 * ((1 - w) * HKD + k2) + 8 * lg)]), sfx[k2],
+                                y[i], 0, 0, 0);
+                        }
                     }
+                    rfo[nr] = rprime(y, vg, nr);
+                    sRf[0][nr][w][lane] = rfo[nr];
                 }
-                rfo = rprime(y, load_vg(0));
-                sRf[0][w][lane] = rfo;
             }
             // K_{c+1} rows of all four token tiles over this wave's key blocks (the
             // partial products X_{c+1} = K_{c+1} S_{c+1}^T the waves exchange)
@@ -1270,11 +1298,16 @@ __device__ __forceinline__ void state_chain_bf16(const Params& p, const int bid,
             for (int mt = 0; mt < 4; ++mt)
 #pragma unroll
                 for (int k2 = 0; k2 < HKD; ++k2) offY[mt][k2] = kq(16 * mt + l16, 32 * (w * HKD + k2) + 8 * lg);
-            auto cstep = [&](int c, auto SLOT) {   // chunk c = SLOT (mod RING)
-                constexpr int b = decltype(SLOT)::value, bn = (b + 1) % RING, x2 = b & 1;
+            auto cstep = [&](int c, auto SLOT) {   // chunk c = SLOT (mod UN)
+                constexpr int b = decltype(SLOT)::value % RD, bn = (b + 1) % RD, x2 = decltype(SLOT)::value & 1;
                 lds_barrier();   // barrier A_c: S_c halves and R'_c visible
-                const bf16x8 rfx = sRf[x2][1 - w][lane];
-                const bf16x8 rf0 = sel(w == 0, rfo, rfx), rf1 = sel(w == 0, rfx, rfo);
+                bf16x8 rf[NR][2];
+#pragma unroll
+                for (int nr = 0; nr < NR; ++nr) {
+                    const bf16x8 rfx = sRf[x2][nr][1 - w][lane];
+                    rf[nr][0] = sel(w == 0, rfo[nr], rfx);
+                    rf[nr][1] = sel(w == 0, rfx, rfo[nr]);
+                }
                 const float gn = sG[b][CH - 1];
                 bf16x8 wf[NFRAG], ka[HMD][2], ky[4][HKD];
 #pragma unroll
@@ -1292,73 +1325,84 @@ __device__ __forceinline__ void state_chain_bf16(const Params& p, const int bid,
                     for (int k2 = 0; k2 < HKD; ++k2) ky[mt][k2] = *reinterpret_cast<const bf16x8*>(&sK[bn][offY[mt][k2]]);
                 const VG vg = load_vg(bn);
                 // D U = W R' (lower triangular: tile mt needs blocks 0..mt/2); S^T <- gn S^T + K^T (D U)
-                floatx4 du[4];
 #pragma unroll
-                for (int mt = 0; mt < 4; ++mt) {
-                    du[mt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wf[frag_id(mt, 0)], rf0, floatx4{0.f, 0.f, 0.f, 0.f},
-                                                                     0, 0, 0);
-                    if (mt >= 2) du[mt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wf[frag_id(mt, 1)], rf1, du[mt], 0, 0, 0);
-                }
-                const bf16x8 df0 = pack_bf16(du[0], du[1]), df1 = pack_bf16(du[2], du[3]);
+                for (int nr = 0; nr < NR; ++nr) {
+                    floatx4 du[4];
 #pragma unroll
-                for (int m = 0; m < HMD; ++m) {
-                    acc[m] *= gn;
-                    acc[m] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ka[m][0], df0, acc[m], 0, 0, 0);
-                    acc[m] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ka[m][1], df1, acc[m], 0, 0, 0);
+                    for (int mt = 0; mt < 4; ++mt) {
+                        du[mt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wf[frag_id(mt, 0)], rf[nr][0],
+                                                                         floatx4{0.f, 0.f, 0.f, 0.f}, 0, 0, 0);
+                        if (mt >= 2)
+                            du[mt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wf[frag_id(mt, 1)], rf[nr][1], du[mt], 0, 0, 0);
+                    }
+                    const bf16x8 df0 = pack_bf16(du[0], du[1]), df1 = pack_bf16(du[2], du[3]);
+#pragma unroll
+                    for (int m = 0; m < HMD; ++m) {
+                        acc[nr][m] *= gn;
+                        acc[nr][m] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ka[m][0], df0, acc[nr][m], 0, 0, 0);
+                        acc[nr][m] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ka[m][1], df1, acc[nr][m], 0, 0, 0);
+                    }
                 }
                 if constexpr (SNAP) {   // S_{c+1}, the state after c + 1 chunks
                     if ((c + 1) % p.snap_every == 0 && c + 1 < nc) {
                         float* sn = p.snaps + (((long)s * p.n_snap + (c + 1) / p.snap_every - 1) * H + h) * (long)DV * DK +
-                                    (long)(js * SL + l16) * DK;
+                                    (long)(js * ROWS) * DK;
 #pragma unroll
-                        for (int m = 0; m < HMD; ++m) *reinterpret_cast<floatx4*>(sn + chan(w * HMD + m)) = acc[m];
+                        for (int nr = 0; nr < NR; ++nr)
+#pragma unroll
+                            for (int m = 0; m < HMD; ++m)
+                                *reinterpret_cast<floatx4*>(sn + (SL * nr + l16) * DK + chan(w * HMD + m)) = acc[nr][m];
                     }
                 }
                 // S_{c+1}: this wave's half for the output waves, and its share of X_{c+1}
                 publish_s(1 - x2);
-                floatx4 yp[4];
+                floatx4 own[NR][2];
 #pragma unroll
-                for (int mt = 0; mt < 4; ++mt) {
-                    yp[mt] = floatx4{0.f, 0.f, 0.f, 0.f};
+                for (int nr = 0; nr < NR; ++nr) {
+                    floatx4 yp[4];
 #pragma unroll
-                    for (int k2 = 0; k2 < HKD; ++k2)
-                        yp[mt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ky[mt][k2], sfo[k2], yp[mt], 0, 0, 0);
-                }
-                // (whole-value selects: a runtime index into a register array would go to scratch)
-                floatx4 own[2], oth[2];
+                    for (int mt = 0; mt < 4; ++mt) {
+                        yp[mt] = floatx4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-                for (int i = 0; i < 2; ++i) {
-                    own[i] = w == 0 ? yp[i] : yp[2 + i];
-                    oth[i] = w == 0 ? yp[2 + i] : yp[i];
-                    sY[w][i][lane] = oth[i];   // the other wave's token tiles
+                        for (int k2 = 0; k2 < HKD; ++k2)
+                            yp[mt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ky[mt][k2], sfo[nr][k2], yp[mt], 0, 0, 0);
+                    }
+#pragma unroll
+                    for (int i = 0; i < 2; ++i) {
+                        own[nr][i] = w == 0 ? yp[i] : yp[2 + i];
+                        sY[nr][w][i][lane] = w == 0 ? yp[2 + i] : yp[i];   // the other wave's token tiles
+                    }
                 }
                 lds_barrier();   // barrier B_c: both waves' shares of X_{c+1} visible
-                floatx4 y[2];
 #pragma unroll
-                for (int i = 0; i < 2; ++i) y[i] = own[i] + sY[1 - w][i][lane];
-                // R'_{c+1}, published for chunk c+1
-                rfo = rprime(y, vg);
-                sRf[1 - x2][w][lane] = rfo;
+                for (int nr = 0; nr < NR; ++nr) {
+                    floatx4 y[2];
+#pragma unroll
+                    for (int i = 0; i < 2; ++i) y[i] = own[nr][i] + sY[nr][1 - w][i][lane];
+                    // R'_{c+1}, published for chunk c+1
+                    rfo[nr] = rprime(y, vg, nr);
+                    sRf[1 - x2][nr][w][lane] = rfo[nr];
+                }
             };
-            for (int c = 0; c < nc; c += RING) {
-                cstep(c, Ic<0>{});
-                if (c + 1 < nc) cstep(c + 1, Ic<1>{});
-                if (c + 2 < nc) cstep(c + 2, Ic<2>{});
-                if (c + 3 < nc) cstep(c + 3, Ic<3>{});
-            }
+            chunks(cstep);
             if constexpr (IDENT) {
-                bf16_t* st = reinterpret_cast<bf16_t*>(p.ST) + srow0 - (long)js * SL * DK + js * SL + l16;
+                bf16_t* st = reinterpret_cast<bf16_t*>(p.ST) + srow0 - (long)js * ROWS * DK + js * ROWS + l16;
 #pragma unroll
-                for (int m = 0; m < HMD; ++m)
+                for (int nr = 0; nr < NR; ++nr)
 #pragma unroll
-                    for (int e = 0; e < 4; ++e) st[(long)(chan(w * HMD + m) + e) * DV] = from_f<bf16_t>(acc[m][e]);
+                    for (int m = 0; m < HMD; ++m)
+#pragma unroll
+                        for (int e = 0; e < 4; ++e)
+                            st[(long)(chan(w * HMD + m) + e) * DV + SL * nr] = from_f<bf16_t>(acc[nr][m][e]);
             } else if (p.ST) {
-                if (FUSED && lds.failed)
+                const float nan = __builtin_nanf("");
+                const bool bad = FUSED && lds.failed;
 #pragma unroll
-                    for (int m = 0; m < HMD; ++m) acc[m] = floatx4{__builtin_nanf(""), __builtin_nanf(""), __builtin_nanf(""), __builtin_nanf("")};
+                for (int nr = 0; nr < NR; ++nr)
 #pragma unroll
-                for (int m = 0; m < HMD; ++m)
-                    *reinterpret_cast<floatx4*>(p.ST + srow0 + l16 * DK + chan(w * HMD + m)) = acc[m];
+                    for (int m = 0; m < HMD; ++m)
+                        *reinterpret_cast<floatx4*>(p.ST + srow0 + (SL * nr + l16) * DK + chan(w * HMD + m)) =
+                            bad ? floatx4{nan, nan, nan, nan} : acc[nr][m];
             }
         };
         if (wave == 0) chain(Ic<0>{});
@@ -1400,10 +1444,10 @@ __device__ __forceinline__ void state_chain_bf16(const Params& p, const int bid,
             // its flag two chunks earlier; with two launches the chunk terms came
             // first.)
             constexpr int NQ = 32 / RPI;
-            bf16x8 pS[RING][NPP];   // P' fragments by ring slot
+            bf16x8 pS[UN][NPP];   // P' fragments by chunk mod UN (two chunks ahead: three sets are live at most)
             auto ostep = [&](int c, auto SLOT) {
-                constexpr int b = decltype(SLOT)::value, x2 = b & 1;
-                const bf16x8(&pa)[NPP] = pS[b];
+                constexpr int u = decltype(SLOT)::value, b = u % RD, x2 = u & 1;
+                const bf16x8(&pa)[NPP] = pS[u];
                 bf16_t* sq = sQ[x2][ow];
                 lds_barrier();   // barrier A_c: S_c and R'_c visible
                 asm volatile("s_waitcnt vmcnt(%0)" ::"n"(NPP + NQ) : "memory");   // Q_c staged, P'_c loaded
@@ -1415,43 +1459,50 @@ __device__ __forceinline__ void state_chain_bf16(const Params& p, const int bid,
                         qa[i][kk] = *reinterpret_cast<const bf16x8*>(sq + kq(16 * i + l16, 32 * kk + 8 * lg));
                 asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // staging buffer read: free for Q_{c+2}
                 if constexpr (!FUSED) {
-                    load_p(min(c + 2, nc - 1), pS[(b + 2) % RING]);
+                    load_p(min(c + 2, nc - 1), pS[(u + 2) % UN]);
                     load_q(min(c + 2, nc - 1), sq);
                 }
-                const bf16x8 rf0 = sRf[x2][0][lane], rf1 = sRf[x2][1][lane];
                 const auto ro = crsrc(p.o, DV, c);
                 typedef int int2v __attribute__((ext_vector_type(2)));
-                int2v ovs[2];
-                auto store_o = [&](int i) {   // 4 value channels of token 16 (2 ow + i) + l16
-                    __builtin_amdgcn_raw_buffer_store_b64(ovs[i], ro, ((16 * (2 * ow + i) + l16) * H * DV + js * SL + 4 * lg) * 2,
-                                                          0, 0);
+                int2v ovs[NR][2];
+                auto store_o = [&](int nr, int i) {   // 4 value channels of token 16 (2 ow + i) + l16
+                    __builtin_amdgcn_raw_buffer_store_b64(
+                        ovs[nr][i], ro, ((16 * (2 * ow + i) + l16) * H * DV + js * ROWS + SL * nr + 4 * lg) * 2, 0, 0);
                 };
 #pragma unroll
-                for (int i = 0; i < 2; ++i) {
-                    const int mt = 2 * ow + i, tok = 16 * mt + l16;
-                    const float gm = sGq[b][tok];
-                    floatx4 oq = {0.f, 0.f, 0.f, 0.f};
+                for (int nr = 0; nr < NR; ++nr) {
+                    const bf16x8 rf0 = sRf[x2][nr][0][lane], rf1 = sRf[x2][nr][1][lane];
 #pragma unroll
-                    for (int kk = 0; kk < NKD; ++kk)
-                        oq = __builtin_amdgcn_mfma_f32_16x16x32_bf16(sSf[x2][kk][lane], qa[i][kk], oq, 0, 0, 0);
-                    floatx4 op;
-                    if constexpr (ow == 0) {
-                        op = __builtin_amdgcn_mfma_f32_16x16x32_bf16(rf0, pa[i], floatx4{0.f, 0.f, 0.f, 0.f}, 0, 0, 0);
-                    } else {   // fragments (mt, 0) = pa[2 i], (mt, 1) = pa[2 i + 1]
-                        op = __builtin_amdgcn_mfma_f32_16x16x32_bf16(rf0, pa[2 * i], floatx4{0.f, 0.f, 0.f, 0.f}, 0, 0, 0);
-                        op = __builtin_amdgcn_mfma_f32_16x16x32_bf16(rf1, pa[2 * i + 1], op, 0, 0, 0);
+                    for (int i = 0; i < 2; ++i) {
+                        const int mt = 2 * ow + i, tok = 16 * mt + l16;
+                        const float gm = sGq[b][tok];
+                        floatx4 oq = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                        for (int kk = 0; kk < NKD; ++kk)
+                            oq = __builtin_amdgcn_mfma_f32_16x16x32_bf16(sSf[x2][nr][kk][lane], qa[i][kk], oq, 0, 0, 0);
+                        floatx4 op;
+                        if constexpr (ow == 0) {
+                            op = __builtin_amdgcn_mfma_f32_16x16x32_bf16(rf0, pa[i], floatx4{0.f, 0.f, 0.f, 0.f}, 0, 0, 0);
+                        } else {   // fragments (mt, 0) = pa[2 i], (mt, 1) = pa[2 i + 1]
+                            op = __builtin_amdgcn_mfma_f32_16x16x32_bf16(rf0, pa[2 * i], floatx4{0.f, 0.f, 0.f, 0.f}, 0, 0, 0);
+                            op = __builtin_amdgcn_mfma_f32_16x16x32_bf16(rf1, pa[2 * i + 1], op, 0, 0, 0);
+                        }
+                        floatx4 ov = p.scale * (gm * oq + op);   // value channels 16 nr + 4 lg .. + 3 of token tok
+                        if (FUSED && lds.failed)
+                            ov = floatx4{__builtin_nanf(""), __builtin_nanf(""), __builtin_nanf(""), __builtin_nanf("")};
+                        ovs[nr][i] = __builtin_bit_cast(int2v, __builtin_convertvector(ov, bf16x4));
+                        if constexpr (!FUSED) store_o(nr, i);
                     }
-                    floatx4 ov = p.scale * (gm * oq + op);   // value channels 4 lg .. 4 lg + 3 of token tok
-                    if (FUSED && lds.failed) ov = floatx4{__builtin_nanf(""), __builtin_nanf(""), __builtin_nanf(""), __builtin_nanf("")};
-                    ovs[i] = __builtin_bit_cast(int2v, __builtin_convertvector(ov, bf16x4));
-                    if constexpr (!FUSED) store_o(i);
                 }
                 lds_barrier();   // B_c (the chain waves' exchange of X_{c+1}); S_c and R'_c are no longer read
                 if constexpr (FUSED) {
-                    load_p(min(c + 2, nc - 1), pS[(b + 2) % RING]);
+                    load_p(min(c + 2, nc - 1), pS[(u + 2) % UN]);
                     load_q(min(c + 2, nc - 1), sq);
-                    store_o(0);
-                    store_o(1);
+#pragma unroll
+                    for (int nr = 0; nr < NR; ++nr) {
+                        store_o(nr, 0);
+                        store_o(nr, 1);
+                    }
                 }
             };
             if (nc > 0) {   // Q is an input: staged while the first chunk terms are formed
@@ -1466,12 +1517,7 @@ __device__ __forceinline__ void state_chain_bf16(const Params& p, const int bid,
             }
             asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // (the first chunks' waits assume the steady-state order)
             lds_barrier();   // prologue 2
-            for (int c = 0; c < nc; c += RING) {   // unrolled so ring slot and fragment set are constants
-                ostep(c, Ic<0>{});
-                if (c + 1 < nc) ostep(c + 1, Ic<1>{});
-                if (c + 2 < nc) ostep(c + 2, Ic<2>{});
-                if (c + 3 < nc) ostep(c + 3, Ic<3>{});
-            }
+            chunks(ostep);
             asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
         };
         if (wave == 2) run(Ic<0>{});
@@ -1480,10 +1526,10 @@ __device__ __forceinline__ void state_chain_bf16(const Params& p, const int bid,
 }
 
 // One workgroup per CU (its LDS), so two waves per SIMD: the register budget is that of two waves.
-template <int DK, bool SNAP = false, bool NORM = false>
+template <int DK, int NR, bool SNAP = false, bool NORM = false>
 __global__ __launch_bounds__(NT_CHAIN) __attribute__((amdgpu_waves_per_eu(1, 2))) void k_state_chain_bf16(Params p) {
-    __shared__ ChainLds<DK> lds;
-    state_chain_bf16<DK, false, false, SNAP, NORM>(p, blockIdx.x, lds);
+    __shared__ ChainLds<DK, NR> lds;
+    state_chain_bf16<DK, NR, false, false, SNAP, NORM>(p, blockIdx.x, lds);
 }
 
 // ------------------------------------------------------------------ bf16 chunk terms
@@ -1811,7 +1857,7 @@ template <int DK, bool SNAP = false, bool NORM = false>
 __global__ __launch_bounds__(NT_CHAIN) __attribute__((amdgpu_waves_per_eu(1, 2))) void k_prefill_fused_bf16(Params p) {
     __shared__ union Lds {
         __device__ Lds() {}
-        ChainLds<DK> c;
+        ChainLds<DK, 1> c;
         struct {
             TermsLds t;
             bf16_t vsink[512];
@@ -1840,7 +1886,7 @@ __global__ __launch_bounds__(NT_CHAIN) __attribute__((amdgpu_waves_per_eu(1, 2))
         }
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // the copies into vsink
     } else {
-        state_chain_bf16<DK, true, false, SNAP, NORM>(p, blockIdx.x - p.npw, lds.c);
+        state_chain_bf16<DK, 1, true, false, SNAP, NORM>(p, blockIdx.x - p.npw, lds.c);
     }
 }
 
@@ -2197,13 +2243,13 @@ struct ChainAlt {
 template <int DK, bool NORM = false>
 __global__ __launch_bounds__(NT_CHAIN) __attribute__((amdgpu_waves_per_eu(1, 2))) void k_state_chain_pair_bf16(Params p,
                                                                                                          ChainAlt a) {
-    __shared__ ChainLds<DK> lds;
+    __shared__ ChainLds<DK, 1> lds;
     const int bid = blockIdx.x;
     if (bid >= a.first) {
         p.v = a.v; p.S0 = a.S0; p.o = a.o; p.ST = a.ST; p.st_t = a.st_t; p.DV = a.DV;
-        state_chain_bf16<DK, false, true, false, NORM>(p, bid - a.first, lds);
+        state_chain_bf16<DK, 1, false, true, false, NORM>(p, bid - a.first, lds);
     } else {
-        state_chain_bf16<DK, false, false, false, NORM>(p, bid, lds);
+        state_chain_bf16<DK, 1, false, false, false, NORM>(p, bid, lds);
     }
 }
 
@@ -2629,11 +2675,23 @@ void launch_prefill(Params p, long slots, hipStream_t st) {
         else
             hipLaunchKernelGGL((k_chunk_terms<DK>), dim3((unsigned)(slots * p.H)), dim3(NT_T32), 0, st, p);
     }
-    const dim3 grid((unsigned)(p.n_seq * p.H * (p.DV / SL)));
-    if constexpr (sizeof(IO) == 2)
-        hipLaunchKernelGGL((k_state_chain_bf16<DK, SNAP, NORM>), grid, dim3(NT_CHAIN), 0, st, p);
+    if constexpr (sizeof(IO) == 2) {
+        // Two row groups per workgroup when that saves rounds: a chunk step of 32 state rows takes
+        // about 1.3 times one of 16 (measured at 16 heads of 128, d = 128, one and two groups: 2 x 4096 tokens,
+        // 256 and 128 workgroups: 85 and 101 us; 3 x 1500 tokens, 384 and 192: 65 and 51; 4 x 1000: 53
+        // and 40; 8 packed prompts, 17481 tokens, 1024 and 512: 213 and 164).  Packed prompts differ in
+        // length, so their workgroups spread better over the CUs than rounds say (3 prompts of 300 to
+        // 2000 tokens, 384 and 192: 55 and 60 us): there from two workgroups per CU on.
+        const long cus = std::max(1, stream_cus(st)), wgs = (long)p.n_seq * p.H * (p.DV / SL);
+        const auto rounds = [&](long n) { return (double)((n + cus - 1) / cus); };
+        const bool two = p.ragged ? wgs >= 2 * cus : 1.3 * rounds(wgs / 2) < rounds(wgs);
+        if (two)
+            hipLaunchKernelGGL((k_state_chain_bf16<DK, 2, SNAP, NORM>), dim3((unsigned)(wgs / 2)), dim3(NT_CHAIN), 0, st, p);
+        else
+            hipLaunchKernelGGL((k_state_chain_bf16<DK, 1, SNAP, NORM>), dim3((unsigned)wgs), dim3(NT_CHAIN), 0, st, p);
+    }
     else
-        hipLaunchKernelGGL((k_state_chain<DK, SNAP>), grid, dim3(NT_CHAIN), 0, st, p);
+        hipLaunchKernelGGL((k_state_chain<DK, SNAP>), dim3((unsigned)(p.n_seq * p.H * (p.DV / SL))), dim3(NT_CHAIN), 0, st, p);
 }
 
 // ---- evaluation plans: sequential chain, segment-parallel (narrow and wide); workspace; launches
