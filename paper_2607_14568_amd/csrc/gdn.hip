@@ -142,6 +142,7 @@ struct Params {
     float* snaps;        // state snapshots [n_seq, n_snap, H, DV, dk] (the SNAP kernels only)
     int snap_every;      // ... after every snap_every chunks of a sequence, strictly inside it
     int n_snap;
+    int term_waves;      // ... and the waves of each that form chunk terms
 };
 
 // Entry i of a sequence table, read where every lane of the wave reads the same
@@ -1006,6 +1007,9 @@ __device__ __forceinline__ void state_chain_bf16(const Params& p, const int bid,
     constexpr int NCH = DK / 8;         // 16-byte chunks per K row
     constexpr int RPI = 64 / NCH;       // rows per 1 KB direct load
     const int H = p.H, DV = p.DV;
+    // (read once: taken from p inside the chunk loop, the compiler keeps a copy per thread in LDS)
+    float* const snaps = p.snaps;
+    const int snap_every = p.snap_every, n_snap = p.n_snap;
     // Workgroups go longest sequence first (ragged), and within a sequence
     // slice-major, so the slices of one (sequence, head) are congruent modulo H:
     // with 8 | H they share an XCD (dispatch is round-robin over the 8 XCDs) and
@@ -1344,8 +1348,8 @@ __device__ __forceinline__ void state_chain_bf16(const Params& p, const int bid,
                     }
                 }
                 if constexpr (SNAP) {   // S_{c+1}, the state after c + 1 chunks
-                    if ((c + 1) % p.snap_every == 0 && c + 1 < nc) {
-                        float* sn = p.snaps + (((long)s * p.n_snap + (c + 1) / p.snap_every - 1) * H + h) * (long)DV * DK +
+                    if ((c + 1) % snap_every == 0 && c + 1 < nc) {
+                        float* sn = snaps + (((long)s * n_snap + (c + 1) / snap_every - 1) * H + h) * (long)DV * DK +
                                     (long)(js * ROWS) * DK;
 #pragma unroll
                         for (int nr = 0; nr < NR; ++nr)
@@ -1847,12 +1851,12 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2, 2))) void
 // the first wave of every workgroup), the rest are chain workgroups.  The
 // chunk-terms workgroups are dispatched first and never wait, so the chain
 // workgroups' waits end whatever number of workgroups the device holds at once.
-// Two waves form chunk terms in each such workgroup: enough to stay ahead of the
-// chain (16 heads consume 16 items per 0.74 us; an item takes about 9 us, 256 at
-// once).  More waves run further ahead than the L2s hold, so the chain finds its K,
-// Q and V rows gone from them, and crowd its loads: with 1, 2, 3, 4 and 8 waves the
-// call of 10240 tokens and 16 heads took 160, 131.7, 140, 145 and 154 us.
-constexpr int TERM_WAVES = 2;
+// p.term_waves waves form chunk terms in each such workgroup, about 256 in all: enough
+// to stay ahead of the chain (16 heads consume 16 items per 0.74 us; an item takes
+// about 9 us).  More run further ahead than the L2s hold, so the chain finds its K,
+// Q and V rows gone from them, and crowd its loads: with 1, 2, 3, 4 and 8 waves in each
+// of 128 workgroups the call of 10240 tokens and 16 heads took 160, 131.7, 140, 145 and 154 us.
+constexpr int TERM_WAVES_MAX = NT_CHAIN / 64, TERM_WAVES_ALL = 256;
 template <int DK, bool SNAP = false, bool NORM = false>
 __global__ __launch_bounds__(NT_CHAIN) __attribute__((amdgpu_waves_per_eu(1, 2))) void k_prefill_fused_bf16(Params p) {
     __shared__ union Lds {
@@ -1861,11 +1865,11 @@ __global__ __launch_bounds__(NT_CHAIN) __attribute__((amdgpu_waves_per_eu(1, 2))
         struct {
             TermsLds t;
             bf16_t vsink[512];
-        } t[TERM_WAVES];
+        } t[TERM_WAVES_MAX];
     } lds;
     if ((int)blockIdx.x < p.npw) {
         const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
-        if (wave >= TERM_WAVES) return;
+        if (wave >= p.term_waves) return;
         auto& my = lds.t[wave];
         if (p.xcd_items) {
             // Dispatch deals workgroups to the 8 XCDs round-robin, so chain
@@ -1875,13 +1879,13 @@ __global__ __launch_bounds__(NT_CHAIN) __attribute__((amdgpu_waves_per_eu(1, 2))
             const int H = p.H, hu = H / 8, q = blockIdx.x / 8, nq = p.npw / 8;
             const int h0 = ((int)(blockIdx.x % 8) - p.npw % 8 + 8) % 8;
             const long items = (long)p.NC * p.n_seq * hu;   // per XCD
-            for (long j = (long)wave * nq + q; j < items; j += (long)TERM_WAVES * nq) {
+            for (long j = (long)wave * nq + q; j < items; j += (long)p.term_waves * nq) {
                 const int c = (int)(j / ((long)p.n_seq * hu)), r = (int)((j / hu) % p.n_seq), u = (int)(j % hu);
                 chunk_terms_bf16<DK, true, NORM>(p, ((long)r * p.NC + c) * H + h0 + 8 * u, my.t, lane, my.vsink);
             }
         } else {
             const long items = (long)(p.ragged ? tab(p.chunk_off, p.n_seq) : p.n_seq * p.NC) * p.H;
-            for (long k = (long)wave * p.npw + blockIdx.x; k < items; k += (long)TERM_WAVES * p.npw)
+            for (long k = (long)wave * p.npw + blockIdx.x; k < items; k += (long)p.term_waves * p.npw)
                 chunk_terms_bf16<DK, true, NORM>(p, item_slot(p, k), my.t, lane, my.vsink);
         }
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // the copies into vsink
@@ -2660,9 +2664,10 @@ void launch_prefill(Params p, long slots, hipStream_t st) {
         const long cus = stream_cus(st);
         const long spare = cus - nchain;   // CUs the chain leaves free (one chain workgroup per CU)
         if (spare >= 8 && 4 * spare >= cus && items > 0) {
-            p.npw = (int)std::min(spare, (items + TERM_WAVES - 1) / TERM_WAVES);
+            p.npw = (int)std::min(spare, items);
             p.xcd_items = !p.ragged && p.H % 8 == 0 && p.npw >= 8;
             if (p.xcd_items) p.npw &= ~7;
+            p.term_waves = std::max(1, std::min(TERM_WAVES_MAX, (TERM_WAVES_ALL + p.npw - 1) / p.npw));
             p.epoch = next_epoch();
             hipLaunchKernelGGL((k_prefill_fused_bf16<DK, SNAP, NORM>), dim3((unsigned)(p.npw + nchain)), dim3(NT_CHAIN), 0,
                                st, p);
@@ -3068,6 +3073,7 @@ static gdn_status prefill(const void* q, const void* k, const void* v, const flo
     p.wait_bound = (flags & GDN_TEST_WITHHOLD) ? 1 << 10 : 1 << 22;
     p.withhold = (flags & GDN_TEST_WITHHOLD) != 0;
     p.npw = 0;
+    p.term_waves = 0;
     p.xcd_items = 0;
     p.scale = scale;
     p.pre = pre;
