@@ -382,12 +382,19 @@ __device__ __forceinline__ void mma3x(bf16x8 ah, bf16x8 al, bf16x8 bh, bf16x8 bl
 }
 
 // ------------------------------------------------------------------ fp32 io: operand images
-// The fp32 chain takes K, Q, T and P as high and low bf16 parts, copied from the
-// workspace straight into LDS; the chunk terms write them in the LDS order.
-// K and Q (64 x dk): the 16-byte pieces of row r sit XOR-swizzled by f32_kq_swz(r),
-// so the row reads (16 rows) and the transpose reads (4 rows, 4 pieces) of the chain
-// meet no bank twice.  T and P (64 x 64): piece j of row r at j ^ (r % 8).
+// The fp32 chain takes K, Q, T and P as high and low bf16 parts, which the chunk terms
+// write in the order it reads them.  K and T are copied from the workspace straight into LDS:
+// K (64 x dk) with the 16-byte pieces of row r XOR-swizzled by f32_kq_swz(r), so that the row
+// reads (16 rows) and the transpose reads (4 rows, 4 pieces) of the chain meet no bank twice;
+// T (64 x 64) with piece j of row r at j ^ (r % 8).  Q and P go from memory into the registers
+// of the one wave that uses them, so they lie in operand order: fragment (token tile, 32-long
+// contraction block), 16-byte piece of lane 16 lg + l16 = row l16, columns 8 lg .. + 7 (read as
+// rows, 64 bytes of 16 rows at a time, they would run the load path at a third of its rate).
 template <int DK> __device__ __forceinline__ int f32_kq_swz(int r) { return ((4 * (r & 3)) | ((r >> 2) & 3)) & (DK / 8 - 1); }
+// 16-byte piece pc of row r of Q or P in operand order (NB contraction blocks per row)
+template <int NB> __device__ __forceinline__ int f32_frag_piece(int r, int pc) {
+    return ((r >> 4) * NB + (pc >> 2)) * 64 + (pc & 3) * 16 + (r & 15);
+}
 template <int DK> __device__ __forceinline__ int f32_kq_at(int r, int cc) {
     return r * DK + (((cc >> 3) ^ f32_kq_swz<DK>(r)) << 3) + (cc & 7);
 }
@@ -490,7 +497,7 @@ __global__ __launch_bounds__(NT_T32) void k_chunk_terms(Params p) {
         p.wsG[slot * GS + lane] = __builtin_amdgcn_exp2f((float)x);
     }
     const bool l2 = p.pre & PRE_L2;
-    {   // split each piece: the LDS tiles, and the chain's copy in its LDS order (f32_kq_at); with
+    {   // split each piece: the LDS tiles, and the chain's copy in its order (K f32_kq_at, Q f32_frag_piece); with
         // PRE_L2 the squared row lengths, summed over the NPR consecutive lanes that hold a row
         bf16_t* kq = reinterpret_cast<bf16_t*>(p.wsKQ) + slot * 4 * CH * DK;   // [K hi | K lo | Q hi | Q lo]
 #pragma unroll
@@ -508,8 +515,9 @@ __global__ __launch_bounds__(NT_T32) void k_chunk_terms(Params p) {
             split8(q0, q1, hi, lo);
             *reinterpret_cast<bf16x8*>(&sQh[r][8 * pc]) = hi;
             *reinterpret_cast<bf16x8*>(&sQl[r][8 * pc]) = lo;
-            *reinterpret_cast<bf16x8*>(kq + 2 * CH * DK + at) = hi;
-            *reinterpret_cast<bf16x8*>(kq + 3 * CH * DK + at) = lo;
+            const int qat = 8 * f32_frag_piece<DK / 32>(r, pc);
+            *reinterpret_cast<bf16x8*>(kq + 2 * CH * DK + qat) = hi;
+            *reinterpret_cast<bf16x8*>(kq + 3 * CH * DK + qat) = lo;
             if (l2) {
                 const floatx4 kk2 = k0 * k0 + k1 * k1, qq2 = q0 * q0 + q1 * q1;
                 float sk = kk2[0] + kk2[1] + kk2[2] + kk2[3], sq = qq2[0] + qq2[1] + qq2[2] + qq2[3];
@@ -624,7 +632,7 @@ __global__ __launch_bounds__(NT_T32) void k_chunk_terms(Params p) {
         }
         __syncthreads();
     }
-    // T and P for the chain: high and low bf16 parts in its LDS order (f32_tp_at), zero above the diagonal blocks
+    // T and P for the chain: high and low bf16 parts in its order, zero above the diagonal blocks
     for (int i = tid; i < CH * CH / 8; i += NT_T32) {
         const int r = i / (CH / 8), col = 8 * ((i % (CH / 8)) ^ (r & 7));
         const bool up = (col >> 4) > (r >> 4);
@@ -634,49 +642,53 @@ __global__ __launch_bounds__(NT_T32) void k_chunk_terms(Params p) {
         *reinterpret_cast<bf16x8*>(Tg + 8 * i) = hi;
         *reinterpret_cast<bf16x8*>(Tg + CH * CH + 8 * i) = lo;
         split8(up ? z : f4(&sP[r][col]), up ? z : f4(&sP[r][col + 4]), hi, lo);
-        *reinterpret_cast<bf16x8*>(Pg + 8 * i) = hi;
-        *reinterpret_cast<bf16x8*>(Pg + CH * CH + 8 * i) = lo;
+        const int pat = 8 * f32_frag_piece<CH / 32>(r, col >> 3);
+        *reinterpret_cast<bf16x8*>(Pg + pat) = hi;
+        *reinterpret_cast<bf16x8*>(Pg + CH * CH + pat) = lo;
     }
 }
 
 // ------------------------------------------------------------------ fp32 state chain
-// One workgroup of 8 waves per (sequence, head, 16-row slice of S); chunks in
+// One workgroup of 12 waves per (sequence, head, 16-row slice of S); chunks in
 // order (section 3.2): with S_c the state entering chunk c,
 //   X = K S_c^T,  R = diag(beta) (V - diag(gamma_k) X),  U = T R,
 //   S_{c+1}^T = gamma_n S_c^T + K^T diag(D) U,
 //   O = scale (diag(gamma_q) Q S_c^T + P U).
-// Waves 0-3 compute (wave w: token tile w of X, R, U and O, and the key tiles
-// w + 4 m of the state update); waves 4-7 copy each chunk's operands into LDS
-// with buffer loads to LDS: K, T and P as the high and low bf16 parts the chunk
-// terms left in the workspace (in the LDS order), the V slice, the decay vectors
-// and beta.  Each compute wave loads its own Q rows (split likewise) into
-// registers at the start of the chunk.  Four barriers per chunk:
-//   A_c  chunk c resident; the compute waves read every tile operand they need
-//        (K rows and K^T fragments, T, P) into registers;
-//   A'_c the copy waves issue chunk c+1's copy of K into the same tile;
-//        the compute waves form X, R;
-//   B_c  the copy waves issue the copies of T, P, V and the decay vectors (V and
-//        the decay vectors alternate by chunk parity); the compute waves form U;
-//   C_c  the compute waves update the state and form O.
-// The copy waves wait for their copies before A_{c+1}.  The state slice stays in
-// the compute waves' fp32 accumulators; S, R, U and D U go through LDS as high and
-// low bf16 parts, split once by the wave that forms them.
+// Waves 0-3 compute (wave w: token tile w of X, R and U, and the key tiles w + 4 m
+// of the state update); waves 4-7 form O, wave 4 + w token tile w, one chunk behind,
+// from the published S and U and from Q and P loaded into their own registers;
+// waves 8-11 copy each chunk's K and T (high and low bf16 parts, as the chunk terms
+// left them), V slice, decay vectors and beta into LDS, a chunk ahead, in two
+// buffers by chunk parity.  Three barriers per chunk:
+//   A_c  chunk c resident, S_c published, chunk c-1's buffers free: the compute
+//        waves form X and R, the copies of chunk c+1 go out;
+//   B_c  R visible: U;
+//   C_c  U and D U visible: the state update, S_{c+1} published.
+// The step is bound by those three phases, an LDS round trip and a chain of MFMAs each
+// (without its copies, 54 KB to LDS and 48 KB to registers at dk = 128, it takes as long).  Taking O
+// off the compute waves, and two K and T buffers in place of one that was read into
+// registers whole before its refill (a fourth barrier), took the step from 2.2 to
+// 1.7 us (2048 tokens, 16 heads: the call 88.8 -> 74.9 us; 4 prompts of 999 tokens 111 -> 98).
+// The state slice stays in the compute waves' fp32 accumulators; S, R, U and D U go
+// through LDS as high and low bf16 parts, split once by the wave that forms them.
 // Every fp32 product is three bf16 MFMA products of high and low parts (mma3x);
 // accumulation is fp32.
 template <int DK> struct __attribute__((aligned(16))) F32ChainLds {
-    bf16_t kq[2][CH * DK];                            // K hi, K lo (f32_kq_at)
-    bf16_t tp[4][CH * CH];                            // T hi, T lo, P hi, P lo (f32_tp_at)
-    bf16_t Sb[2][2][SL][DK + 8];                      // the slice of S, high and low parts, by chunk parity
-    float V[2][CH * SL];                              // [token][value channel of the slice], by chunk parity
-    float g[2][5 * CH];                               // gamma, D, gamma s_k, gamma s_q, beta; by chunk parity
+    bf16_t k[2][2][CH * DK];                          // by chunk parity: K hi, K lo (f32_kq_at)
+    bf16_t t[2][2][CH * CH];                          // ... T hi, T lo (f32_tp_at)
+    float V[2][CH * SL];                              // ... [token][value channel of the slice]
+    float g[2][5 * CH];                               // ... gamma, D, gamma s_k, gamma s_q, beta
+    bf16_t Sb[2][2][SL][DK + 8];                      // ... the slice of S, high and low parts
     bf16_t Rb[2][SL][CH + 8];                         // R transposed, high and low parts
     bf16_t Ub[4][SL][CH + 8];                         // U and D U transposed, high and low parts
 };
+constexpr int NT_CHAIN_F32 = 768;
 
 template <int DK, bool SNAP = false>
 __device__ __forceinline__ void state_chain_f32(const Params& p, const int bid, F32ChainLds<DK>& lds) {
     constexpr int NKD = DK / 32;          // 32-long contraction blocks over the key channels
     constexpr int NMW = DK / 64;          // 16-key tiles of S^T per compute wave in the state update
+    constexpr int KQB = 4 * CH * DK * 2, TPB = 2 * CH * CH * 2;   // bytes per (slot, head): K and Q; T or P
     const int H = p.H, DV = p.DV, nsl = DV / SL;
     // slice-major: the slices of one (sequence, head) are congruent modulo H, so with
     // 8 | H they share an XCD (dispatch deals workgroups to the 8 XCDs in turn) and
@@ -692,53 +704,122 @@ __device__ __forceinline__ void state_chain_f32(const Params& p, const int bid, 
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int l16 = lane & 15, lg = lane >> 4;
     const long srow0 = ((long)(s * H + h) * DV + js * SL) * DK;
+    const bool l2 = p.pre & PRE_L2;
+    const floatx4 z4 = {0.f, 0.f, 0.f, 0.f};
 
-    if (wave >= 4) {
+    if (wave >= 8) {
         // ------------------------------------------------ copy waves
-        const int li = wave - 4;
-        constexpr int KQB = 4 * CH * DK * 2, TPB = 2 * CH * CH * 2;   // bytes per (slot, head)
-        // K (hi, lo): the first half of the K/Q image (the compute waves load their Q rows themselves)
-        auto issue_k = [&](int c) {
-            const long slot = (long)(cbase + c) * H + h;
-            const auto rk = rsrc(reinterpret_cast<const char*>(p.wsKQ) + slot * KQB, KQB / 2);
-#pragma unroll
-            for (int i = li; i < KQB / 2048; i += 4) bdma16(rk, reinterpret_cast<char*>(&lds.kq[0][0]) + i * 1024, i * 1024 + lane * 16);
-        };
-        auto issue_rest = [&](int c) {
+        const int li = wave - 8;
+        auto issue = [&](int c) {
+            const int b = c & 1;
             const long slot = (long)(cbase + c) * H + h, t0 = start + (long)c * CH;
             const int n = min(CH, len - c * CH);
+            const auto rk = rsrc(reinterpret_cast<const char*>(p.wsKQ) + slot * KQB, KQB / 2);   // K: the first half of the K/Q image
             const auto rt = rsrc(reinterpret_cast<const char*>(p.wsT) + slot * TPB, TPB);
-            const auto rp = rsrc(reinterpret_cast<const char*>(p.wsP) + slot * TPB, TPB);
 #pragma unroll
-            for (int i = li; i < TPB / 1024; i += 4) {
-                bdma16(rt, reinterpret_cast<char*>(&lds.tp[0][0]) + i * 1024, i * 1024 + lane * 16);
-                bdma16(rp, reinterpret_cast<char*>(&lds.tp[2][0]) + i * 1024, i * 1024 + lane * 16);
-            }
+            for (int i = 0; i < KQB / 2048; i += 4)
+                bdma16(rk, reinterpret_cast<char*>(&lds.k[b][0][0]) + (i + li) * 1024, (i + li) * 1024 + lane * 16);
             // V rows 16 li .. 16 li + 15 of the slice (no value tensor: zeros); rows past the chunk read as zeros
             const long rb = (long)(n - 1) * H + 1;
             const auto rv = p.v ? rsrc(reinterpret_cast<const float*>(p.v) + (t0 * H + h) * DV, (uint32_t)(rb * DV * 4))
                                 : rsrc(p.k, 0u);
-            bdma16(rv, &lds.V[c & 1][16 * li * SL], ((16 * li + lane / 4) * H * DV + js * SL + 4 * (lane % 4)) * 4);
-            if (li == 0) bdma16(rsrc(p.wsG + slot * GS, GS * 4), &lds.g[c & 1][0], lane * 16);
-            if (li == 1) bdma4(rsrc(p.beta + t0 * H + h, (uint32_t)(rb * 4)), &lds.g[c & 1][4 * CH], lane * H * 4);
+            bdma16(rv, &lds.V[b][16 * li * SL], ((16 * li + lane / 4) * H * DV + js * SL + 4 * (lane % 4)) * 4);
+            if (li == 0) bdma16(rsrc(p.wsG + slot * GS, GS * 4), &lds.g[b][0], lane * 16);
+            if (li == 1) bdma4(rsrc(p.beta + t0 * H + h, (uint32_t)(rb * 4)), &lds.g[b][4 * CH], lane * H * 4);
+#pragma unroll
+            for (int i = 0; i < TPB / 1024; i += 4)
+                bdma16(rt, reinterpret_cast<char*>(&lds.t[b][0][0]) + (i + li) * 1024, (i + li) * 1024 + lane * 16);
         };
-        if (nc > 0) {
-            issue_k(0);
-            issue_rest(0);
-        }
-        // the copies of chunk c+1 go out over chunk c's phases (issuing them takes about as
-        // long as their arithmetic; of the splits measured, K after A'_c and the rest after
-        // B_c was the fastest)
+        if (nc > 0) issue(0);
         for (int c = 0; c < nc; ++c) {
             asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
             lds_barrier();   // A_c
-            lds_barrier();   // A'_c
-            if (c + 1 < nc) issue_k(c + 1);
-            lds_barrier();   // B_c
-            if (c + 1 < nc) issue_rest(c + 1);
-            lds_barrier();   // C_c
+            if (c + 1 < nc) issue(c + 1);
+            asm volatile("s_barrier" ::: "memory");   // B_c
+            asm volatile("s_barrier" ::: "memory");   // C_c
         }
-        lds_barrier();   // F
+        return;
+    }
+
+    if (wave >= 4) {
+        // ------------------------------------------------ output waves
+        const int w = wave - 4;
+        bf16x8 qh[NKD], ql[NKD], ph[2], pl[2];
+        floatx4 gq;
+        auto load = [&](int c) {   // token tile w of chunk c: Q, P and gamma_q
+            const long slot = (long)(cbase + c) * H + h;
+            const auto rq = rsrc(reinterpret_cast<const char*>(p.wsKQ) + slot * KQB + KQB / 2, KQB / 2);
+            const auto rp = rsrc(reinterpret_cast<const char*>(p.wsP) + slot * TPB, TPB);
+#pragma unroll
+            for (int kk = 0; kk < NKD; ++kk) {
+                qh[kk] = bload16(rq, (w * NKD + kk) * 1024 + lane * 16);
+                ql[kk] = bload16(rq, CH * DK * 2 + (w * NKD + kk) * 1024 + lane * 16);
+            }
+#pragma unroll
+            for (int kk = 0; kk < 2; ++kk) {
+                ph[kk] = bload16(rp, (w * 2 + kk) * 1024 + lane * 16);
+                pl[kk] = bload16(rp, CH * CH * 2 + (w * 2 + kk) * 1024 + lane * 16);
+            }
+            gq = __builtin_bit_cast(floatx4, bload16(rsrc(p.wsG + slot * GS, GS * 4), ((l2 ? 3 * CH : 0) + 16 * w + 4 * lg) * 4));
+        };
+        bf16x8 sh[NKD], sl[NKD], uh[2], ul[2];
+        auto read_s = [&](int c) {
+#pragma unroll
+            for (int kk = 0; kk < NKD; ++kk) {
+                sh[kk] = *reinterpret_cast<const bf16x8*>(&lds.Sb[c & 1][0][l16][32 * kk + 8 * lg]);
+                sl[kk] = *reinterpret_cast<const bf16x8*>(&lds.Sb[c & 1][1][l16][32 * kk + 8 * lg]);
+            }
+        };
+        auto read_u = [&] {
+#pragma unroll
+            for (int kk = 0; kk < 2; ++kk) {
+                uh[kk] = *reinterpret_cast<const bf16x8*>(&lds.Ub[0][l16][32 * kk + 8 * lg]);
+                ul[kk] = *reinterpret_cast<const bf16x8*>(&lds.Ub[1][l16][32 * kk + 8 * lg]);
+            }
+        };
+        floatx4 qa[3];
+        auto qs = [&] {
+            qa[0] = qa[1] = qa[2] = z4;
+#pragma unroll
+            for (int kk = 0; kk < NKD; ++kk) mma3x(qh[kk], ql[kk], sh[kk], sl[kk], qa);
+        };
+        auto pu_store = [&](int c) {   // O; rows past the chunk fall outside the descriptor and are dropped
+            floatx4 pa[3] = {z4, z4, z4};
+#pragma unroll
+            for (int kk = 0; kk < 2; ++kk) mma3x(ph[kk], pl[kk], uh[kk], ul[kk], pa);
+            const long t0 = start + (long)c * CH;
+            const int n = min(CH, len - c * CH);
+            const floatx4 oq = qa[0] + qa[1] + qa[2], op = pa[0] + pa[1] + pa[2];
+            const auto ro = rsrc(reinterpret_cast<float*>(p.o) + (t0 * H + h) * DV, (uint32_t)((((long)n - 1) * H + 1) * DV * 4));
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const int r = w * 16 + 4 * lg + e;
+                const float ov = p.scale * (gq[e] * oq[e] + op[e]);
+                __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(ov), ro, (r * H * DV + js * SL + l16) * 4, 0, 0);
+            }
+        };
+        if (nc > 0) {
+            load(0);
+            lds_barrier();                            // A_0
+            asm volatile("s_barrier" ::: "memory");   // B_0
+            asm volatile("s_barrier" ::: "memory");   // C_0
+        }
+        for (int c = 1; c < nc; ++c) {   // step c: the outputs of chunk c - 1
+            lds_barrier();   // A_c
+            read_u();        // U_{c-1}: overwritten after B_c
+            lds_barrier();   // B_c
+            read_s(c - 1);   // S_{c-1}: overwritten after C_c
+            qs();
+            asm volatile("s_barrier" ::: "memory");   // C_c
+            pu_store(c - 1);
+            load(c);
+        }
+        if (nc > 0) {
+            read_u();
+            read_s(nc - 1);
+            qs();
+            pu_store(nc - 1);
+        }
         return;
     }
 
@@ -750,8 +831,7 @@ __device__ __forceinline__ void state_chain_f32(const Params& p, const int bid, 
     floatx4 acc[NMW];
 #pragma unroll
     for (int m = 0; m < NMW; ++m)
-        acc[m] = p.S0 ? *reinterpret_cast<const floatx4*>(p.S0 + srow0 + l16 * DK + chan(wave + 4 * m))
-                      : floatx4{0.f, 0.f, 0.f, 0.f};
+        acc[m] = p.S0 ? *reinterpret_cast<const floatx4*>(p.S0 + srow0 + l16 * DK + chan(wave + 4 * m)) : z4;
     auto put_split4 = [](bf16_t* hi, bf16_t* lo, floatx4 v) {   // 4 values -> 8 bytes of each part
         const bf16x4 h4 = __builtin_convertvector(v, bf16x4);
         floatx4 r;
@@ -765,13 +845,11 @@ __device__ __forceinline__ void state_chain_f32(const Params& p, const int bid, 
         for (int m = 0; m < NMW; ++m) put_split4(&lds.Sb[par][0][l16][chan(wave + 4 * m)], &lds.Sb[par][1][l16][chan(wave + 4 * m)], acc[m]);
     };
     if (nc > 0) publish_s(0);
-    const bool l2 = p.pre & PRE_L2, gates = p.pre & PRE_GATES;
+    const bool gates = p.pre & PRE_GATES;
     const int row = wave * 16 + l16;   // token row of this lane's A operands
-    const floatx4 z4 = {0.f, 0.f, 0.f, 0.f};
     for (int c = 0; c < nc; ++c) {
-        const long t0 = start + (long)c * CH;
-        const int n = min(CH, len - c * CH);
-        const float* G = lds.g[c & 1];
+        const int b = c & 1, n = min(CH, len - c * CH);
+        const float* G = lds.g[b];
         lds_barrier();   // A_c
         if constexpr (SNAP) {   // S_c, the state after c chunks
             if (c > 0 && c % p.snap_every == 0) {
@@ -781,36 +859,52 @@ __device__ __forceinline__ void state_chain_f32(const Params& p, const int bid, 
                 for (int m = 0; m < NMW; ++m) *reinterpret_cast<floatx4*>(sn + chan(wave + 4 * m)) = acc[m];
             }
         }
-        // this wave's Q rows (high and low parts) straight from the workspace into registers, for
-        // the output product at the end of the chunk (one LDS pass fewer)
-        bf16x8 kh[NKD], kl[NKD], qh[NKD], ql[NKD], th[2], tl[2], ph[2], pl[2], kth[NMW][2], ktl[NMW][2];
-        {
-            constexpr int KQB = 4 * CH * DK * 2;
-            const auto rq = rsrc(reinterpret_cast<const char*>(p.wsKQ) + ((long)(cbase + c) * H + h) * KQB + KQB / 2, KQB / 2);
-#pragma unroll
-            for (int kk = 0; kk < NKD; ++kk) {
-                const int at = 2 * f32_kq_at<DK>(row, 32 * kk + 8 * lg);   // bytes
-                qh[kk] = bload16(rq, at);
-                ql[kk] = bload16(rq, CH * DK * 2 + at);
-            }
-        }
-        // the tile operands into registers before A'_c (the copy waves refill the tiles after it)
+        // X = K S_c^T, S_c as B operands (key channel 32 kk + 8 lg + j, state row l16)
+        floatx4 xa[3] = {z4, z4, z4};
 #pragma unroll
         for (int kk = 0; kk < NKD; ++kk) {
             const int at = f32_kq_at<DK>(row, 32 * kk + 8 * lg);
-            kh[kk] = *reinterpret_cast<const bf16x8*>(&lds.kq[0][at]);
-            kl[kk] = *reinterpret_cast<const bf16x8*>(&lds.kq[1][at]);
+            mma3x(*reinterpret_cast<const bf16x8*>(&lds.k[b][0][at]), *reinterpret_cast<const bf16x8*>(&lds.k[b][1][at]),
+                  *reinterpret_cast<const bf16x8*>(&lds.Sb[b][0][l16][32 * kk + 8 * lg]),
+                  *reinterpret_cast<const bf16x8*>(&lds.Sb[b][1][l16][32 * kk + 8 * lg]), xa);
         }
+        // R = diag(beta) (V - diag(gamma_k) X) for tokens 16 wave + 4 lg + e; rows past the chunk: beta = 0
+        const floatx4 gk = f4(&G[(l2 ? 2 * CH : 0) + wave * 16 + 4 * lg]), dg = f4(&G[CH + wave * 16 + 4 * lg]);
+        const floatx4 braw = f4(&G[4 * CH + wave * 16 + 4 * lg]);
+        floatx4 bv, vv;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const int r = wave * 16 + 4 * lg + e;
+            bv[e] = r < n ? (gates ? gate_beta(braw[e]) : braw[e]) : 0.f;
+            vv[e] = lds.V[b][r * SL + l16];
+        }
+        const float gn = G[CH - 1];
+        bf16x8 th[2], tl[2];   // T for U
 #pragma unroll
         for (int kk = 0; kk < 2; ++kk) {
             const int at = f32_tp_at(row, 32 * kk + 8 * lg);
-            th[kk] = *reinterpret_cast<const bf16x8*>(&lds.tp[0][at]);
-            tl[kk] = *reinterpret_cast<const bf16x8*>(&lds.tp[1][at]);
-            ph[kk] = *reinterpret_cast<const bf16x8*>(&lds.tp[2][at]);
-            pl[kk] = *reinterpret_cast<const bf16x8*>(&lds.tp[3][at]);
+            th[kk] = *reinterpret_cast<const bf16x8*>(&lds.t[b][0][at]);
+            tl[kk] = *reinterpret_cast<const bf16x8*>(&lds.t[b][1][at]);
         }
-        // K^T fragments of key tiles md = wave + 4 m (transpose reads); contraction element j
-        // of lane group lg in block kk is token 32 kk + 16 (j / 4) + 4 lg + j % 4
+        {
+            const floatx4 x = xa[0] + xa[1] + xa[2];
+            floatx4 rv;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) rv[e] = bv[e] * (vv[e] - gk[e] * x[e]);
+            put_split4(&lds.Rb[0][l16][wave * 16 + 4 * lg], &lds.Rb[1][l16][wave * 16 + 4 * lg], rv);
+        }
+        lds_barrier();   // B_c
+
+        bf16x8 rh[2], rl[2];
+#pragma unroll
+        for (int kk = 0; kk < 2; ++kk) {
+            rh[kk] = *reinterpret_cast<const bf16x8*>(&lds.Rb[0][l16][32 * kk + 8 * lg]);
+            rl[kk] = *reinterpret_cast<const bf16x8*>(&lds.Rb[1][l16][32 * kk + 8 * lg]);
+        }
+        // K^T fragments of key tiles md = wave + 4 m (transpose reads) for the update, read in
+        // this phase because the first one keeps LDS busiest; contraction element j of lane
+        // group lg in block kk is token 32 kk + 16 (j / 4) + 4 lg + j % 4
+        bf16x8 kth[NMW][2], ktl[NMW][2];
 #pragma unroll
         for (int m = 0; m < NMW; ++m) {
             const int md = wave + 4 * m, col = 32 * (md >> 1) + 8 * (l16 & 3) + 4 * (md & 1);
@@ -818,51 +912,23 @@ __device__ __forceinline__ void state_chain_f32(const Params& p, const int bid, 
             for (int kk = 0; kk < 2; ++kk) {
                 const int o0 = f32_kq_at<DK>(32 * kk + 4 * lg + (l16 >> 2), col);
                 const int o1 = f32_kq_at<DK>(32 * kk + 16 + 4 * lg + (l16 >> 2), col);
-                kth[m][kk] = join4(lds_tr8(&lds.kq[0][o0]), lds_tr8(&lds.kq[0][o1]));
-                ktl[m][kk] = join4(lds_tr8(&lds.kq[1][o0]), lds_tr8(&lds.kq[1][o1]));
+                kth[m][kk] = join4(lds_tr8(&lds.k[b][0][o0]), lds_tr8(&lds.k[b][0][o1]));
+                ktl[m][kk] = join4(lds_tr8(&lds.k[b][1][o0]), lds_tr8(&lds.k[b][1][o1]));
             }
         }
-        lds_barrier();   // A'_c
-        // X = K S_c^T, S_c as B operands (key channel 32 kk + 8 lg + j, state row l16)
-        bf16x8 sbh[NKD], sbl[NKD];
-        floatx4 xa[3] = {z4, z4, z4};
-#pragma unroll
-        for (int kk = 0; kk < NKD; ++kk) {
-            sbh[kk] = *reinterpret_cast<const bf16x8*>(&lds.Sb[c & 1][0][l16][32 * kk + 8 * lg]);
-            sbl[kk] = *reinterpret_cast<const bf16x8*>(&lds.Sb[c & 1][1][l16][32 * kk + 8 * lg]);
-            mma3x(kh[kk], kl[kk], sbh[kk], sbl[kk], xa);
-        }
-        {   // R = diag(beta) (V - diag(gamma_k) X) for tokens 16 wave + 4 lg + e; rows past the chunk: beta = 0
-            const floatx4 x = xa[0] + xa[1] + xa[2];
-            floatx4 rv;
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                const int r = wave * 16 + 4 * lg + e;
-                const float braw = G[4 * CH + r];
-                const float b = r < n ? (gates ? gate_beta(braw) : braw) : 0.f;
-                rv[e] = b * (lds.V[c & 1][r * SL + l16] - (l2 ? G[2 * CH + r] : G[r]) * x[e]);
-            }
-            put_split4(&lds.Rb[0][l16][wave * 16 + 4 * lg], &lds.Rb[1][l16][wave * 16 + 4 * lg], rv);
-        }
-        lds_barrier();   // B_c
-
         // U = T R (k = token 32 kk + 8 lg + j); published as U and as D U
         {
             floatx4 ua[3] = {z4, z4, z4};
 #pragma unroll
-            for (int kk = 0; kk < 2; ++kk)
-                mma3x(th[kk], tl[kk], *reinterpret_cast<const bf16x8*>(&lds.Rb[0][l16][32 * kk + 8 * lg]),
-                      *reinterpret_cast<const bf16x8*>(&lds.Rb[1][l16][32 * kk + 8 * lg]), ua);
+            for (int kk = 0; kk < 2; ++kk) mma3x(th[kk], tl[kk], rh[kk], rl[kk], ua);
             const floatx4 u = ua[0] + ua[1] + ua[2];
+            put_split4(&lds.Ub[2][l16][wave * 16 + 4 * lg], &lds.Ub[3][l16][wave * 16 + 4 * lg], dg * u);
             put_split4(&lds.Ub[0][l16][wave * 16 + 4 * lg], &lds.Ub[1][l16][wave * 16 + 4 * lg], u);
-            put_split4(&lds.Ub[2][l16][wave * 16 + 4 * lg], &lds.Ub[3][l16][wave * 16 + 4 * lg],
-                       f4(&G[CH + wave * 16 + 4 * lg]) * u);
         }
         lds_barrier();   // C_c
 
         // S^T <- gamma_n S^T + K^T (D U)
         {
-            const float gn = G[CH - 1];
             bf16x8 dh[2], dl[2];
 #pragma unroll
             for (int kk = 0; kk < 2; ++kk) {
@@ -878,28 +944,9 @@ __device__ __forceinline__ void state_chain_f32(const Params& p, const int bid, 
                 for (int kk = 0; kk < 2; ++kk) mma3x(kth[m][kk], ktl[m][kk], dh[kk], dl[kk], sa);
                 acc[m] = sa[0] + sa[1] + sa[2];
             }
-            publish_s((c + 1) & 1);
-        }
-        // O = scale (diag(gamma_q) Q S_c^T + P U)
-        floatx4 qa[3] = {z4, z4, z4}, pa[3] = {z4, z4, z4};
-#pragma unroll
-        for (int kk = 0; kk < NKD; ++kk) mma3x(qh[kk], ql[kk], sbh[kk], sbl[kk], qa);
-#pragma unroll
-        for (int kk = 0; kk < 2; ++kk)
-            mma3x(ph[kk], pl[kk], *reinterpret_cast<const bf16x8*>(&lds.Ub[0][l16][32 * kk + 8 * lg]),
-                  *reinterpret_cast<const bf16x8*>(&lds.Ub[1][l16][32 * kk + 8 * lg]), pa);
-        {   // rows past the chunk fall outside the descriptor and are dropped
-            const floatx4 oq = qa[0] + qa[1] + qa[2], op = pa[0] + pa[1] + pa[2];
-            const auto ro = rsrc(reinterpret_cast<float*>(p.o) + (t0 * H + h) * DV, (uint32_t)((((long)n - 1) * H + 1) * DV * 4));
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                const int r = wave * 16 + 4 * lg + e;
-                const float ov = p.scale * ((l2 ? G[3 * CH + r] : G[r]) * oq[e] + op[e]);
-                __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(ov), ro, (r * H * DV + js * SL + l16) * 4, 0, 0);
-            }
+            publish_s(1 - b);
         }
     }
-    lds_barrier();   // F
     if (p.ST) {
 #pragma unroll
         for (int m = 0; m < NMW; ++m) {
@@ -914,9 +961,9 @@ __device__ __forceinline__ void state_chain_f32(const Params& p, const int bid, 
     }
 }
 
-// One workgroup per CU (its LDS): two waves per SIMD.
+// One workgroup per CU (its LDS): three waves per SIMD.
 template <int DK, bool SNAP = false>
-__global__ __launch_bounds__(NT_CHAIN) __attribute__((amdgpu_waves_per_eu(1, 2))) void k_state_chain(Params p) {
+__global__ __launch_bounds__(NT_CHAIN_F32) __attribute__((amdgpu_waves_per_eu(3, 3))) void k_state_chain(Params p) {
     __shared__ F32ChainLds<DK> lds;
     state_chain_f32<DK, SNAP>(p, blockIdx.x, lds);
 }
@@ -2258,7 +2305,7 @@ __global__ __launch_bounds__(NT_CHAIN) __attribute__((amdgpu_waves_per_eu(1, 2))
 }
 
 template <int DK>
-__global__ __launch_bounds__(NT_CHAIN) __attribute__((amdgpu_waves_per_eu(1, 2))) void k_state_chain_pair(Params p, ChainAlt a) {
+__global__ __launch_bounds__(NT_CHAIN_F32) __attribute__((amdgpu_waves_per_eu(3, 3))) void k_state_chain_pair(Params p, ChainAlt a) {
     __shared__ F32ChainLds<DK> lds;
     int bid = blockIdx.x;
     if (bid >= a.first) { p.v = a.v; p.S0 = a.S0; p.o = a.o; p.ST = a.ST; p.st_t = a.st_t; p.DV = a.DV; bid -= a.first; }
@@ -2696,7 +2743,7 @@ void launch_prefill(Params p, long slots, hipStream_t st) {
             hipLaunchKernelGGL((k_state_chain_bf16<DK, 1, SNAP, NORM>), dim3((unsigned)wgs), dim3(NT_CHAIN), 0, st, p);
     }
     else
-        hipLaunchKernelGGL((k_state_chain<DK, SNAP>), dim3((unsigned)(p.n_seq * p.H * (p.DV / SL))), dim3(NT_CHAIN), 0, st, p);
+        hipLaunchKernelGGL((k_state_chain<DK, SNAP>), dim3((unsigned)(p.n_seq * p.H * (p.DV / SL))), dim3(NT_CHAIN_F32), 0, st, p);
 }
 
 // ---- evaluation plans: sequential chain, segment-parallel (narrow and wide); workspace; launches
@@ -2874,7 +2921,7 @@ void launch_segmented(Params p, const SegParams& sq, long slots, hipStream_t st)
     if constexpr (sizeof(IO) == 2)
         hipLaunchKernelGGL((k_state_chain_pair_bf16<DK, NORM>), grid, dim3(NT_CHAIN), 0, st, p, a);
     else
-        hipLaunchKernelGGL((k_state_chain_pair<DK>), grid, dim3(NT_CHAIN), 0, st, p, a);
+        hipLaunchKernelGGL((k_state_chain_pair<DK>), grid, dim3(NT_CHAIN_F32), 0, st, p, a);
     const long units = (long)sq.nseq * sq.H;   // (sequence, head) pairs, each on one XCD
     hipLaunchKernelGGL((k_segment_scan<IO, DK>), dim3((unsigned)(8 * ((units + 7) / 8) * (sq.DV / SL))), dim3(DK * 4), 0,
                        st, sq);
