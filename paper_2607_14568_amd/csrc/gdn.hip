@@ -2339,6 +2339,7 @@ struct AttnParams {
     int nqb;            // dense: query blocks per sequence; packed: blocks of the grid per head (an upper bound)
     const int32_t* cu;  // packed sequences: offsets [n_seq + 1] (device), or null
     int n_seq;
+    int longest_first;  // packed: blocks in order of their keys, most first (else sequence by sequence)
     float scale_log2;   // scale * log2(e)
 };
 
@@ -2354,7 +2355,6 @@ __global__ __launch_bounds__(NT_ATT / QT) __attribute__((amdgpu_waves_per_eu(4 /
     constexpr int RPI = 64 / NCH;       // rows per 1 KB copy
     constexpr int NKB = DH / 32;        // contraction blocks over the head dimension
     constexpr int NDT = DH / 16;        // 16-row tiles of O^T
-    constexpr int NCP = 2 * AKB / RPI;  // 1 KB copies per key block (K and V)
     __shared__ AttnLds<DH> lds;
     const int BH = p.B * p.H;
     int qb = p.nqb - 1 - (int)(blockIdx.x / BH);   // blocks with the most keys first
@@ -2367,26 +2367,58 @@ __global__ __launch_bounds__(NT_ATT / QT) __attribute__((amdgpu_waves_per_eu(4 /
     long seq0 = (long)b * p.T;   // first row of this workgroup's sequence
     int T = p.T;                 // its length
     if (p.cu) {
-        // packed sequences (B = 1): grid block qb (counted from the top) is block j of sequence s, where the
-        // sequences' blocks are numbered consecutively, each sequence's last block first.  Offsets outside the
-        // contract are clamped into a nondecreasing partition of [0, p.T], so every access stays in bounds.
-        int prev = 0, before = 0, s = 0;
-        int found = -1;
-        for (; s < p.n_seq; ++s) {
-            const int next = min(max(tab(p.cu, s + 1), prev), p.T);
-            const int nb = (next - prev + AQ - 1) / AQ;
-            const int r = p.nqb - 1 - qb;   // rank of this block in that numbering
-            if (r < before + nb) {
-                found = nb - 1 - (r - before);
-                seq0 = prev;
-                T = next - prev;
-                break;
+        // Packed sequences (B = 1): rank r = 0, 1, .. of the grid's blocks.  Offsets outside the contract are
+        // clamped into a nondecreasing partition of [0, p.T], so every access stays in bounds; ranks past the
+        // last block (the grid is an upper bound) return.
+        const int r = p.nqb - 1 - qb;
+        if (p.longest_first) {
+            // The blocks of all sequences (at most 64: lane s holds sequence s) by their number of keys, most
+            // first: down the block index, sequences in order within one index.
+            int end = lane < p.n_seq ? min(max(p.cu[lane + 1], 0), p.T) : p.T;
+#pragma unroll
+            for (int off = 1; off < 64; off <<= 1) {
+                const int y = __shfl_up(end, off, 64);
+                if (lane >= off) end = max(end, y);
             }
-            before += nb;
-            prev = next;
+            const int prev = __shfl_up(end, 1, 64), beg = lane > 0 ? prev : 0;
+            const int nb = lane < p.n_seq ? (end - beg + AQ - 1) / AQ : 0;
+            auto from = [&](int level) {   // blocks of index >= level
+                int n = max(nb - level, 0);
+#pragma unroll
+                for (int off = 1; off < 64; off <<= 1) n += __shfl_xor(n, off, 64);
+                return __builtin_amdgcn_readfirstlane(n);
+            };
+            if (r >= from(0)) return;
+            int lo = 0, hi = p.nqb;   // from(lo) > r >= from(hi)
+            while (hi - lo > 1) {
+                const int mid = (lo + hi) >> 1;
+                if (from(mid) > r) lo = mid; else hi = mid;
+            }
+            const int pos = r - from(lo + 1);
+            const uint64_t has = __builtin_amdgcn_ballot_w64(nb > lo);
+            const int below = __builtin_popcountll(has & ((1ull << lane) - 1));
+            const int s = __builtin_ctzll(__builtin_amdgcn_ballot_w64(nb > lo && below == pos));
+            seq0 = __builtin_amdgcn_readlane(beg, s);
+            T = __builtin_amdgcn_readlane(end, s) - (int)seq0;
+            qb = lo;
+        } else {
+            // the sequences' blocks numbered consecutively, each sequence's last block first
+            int prev = 0, before = 0, found = -1;
+            for (int s = 0; s < p.n_seq; ++s) {
+                const int next = min(max(tab(p.cu, s + 1), prev), p.T);
+                const int nb = (next - prev + AQ - 1) / AQ;
+                if (r < before + nb) {
+                    found = nb - 1 - (r - before);
+                    seq0 = prev;
+                    T = next - prev;
+                    break;
+                }
+                before += nb;
+                prev = next;
+            }
+            if (found < 0) return;
+            qb = found;
         }
-        if (found < 0) return;   // past the last block (the grid is an upper bound)
-        qb = found;
     }
     const int q0 = qb * AQ, qw = q0 + 16 * QT * wave;   // the workgroup's and this wave's first query
     const long rsq = (long)p.H * DH, rsk = (long)p.HKV * DH;   // row strides (elements)
@@ -2417,19 +2449,24 @@ __global__ __launch_bounds__(NT_ATT / QT) __attribute__((amdgpu_waves_per_eu(4 /
 #pragma unroll
             for (int kb = 0; kb < NKB; ++kb) qf[u][kb] = bload16(rq, (int)(((16 * u + l16) * rsq + 32 * kb + 8 * lg) * 2));
     }
-    // copies of key block j into ring slot j & 1: copy c < NCP / 2 is K rows RPI c .., the rest V
+    // copies of key block j into ring slot j & 1: this wave's 1 KB pieces of K and of V
     const int nkb = min((T + AKB - 1) / AKB, (q0 + AQ) / AKB);
-    auto issue = [&](int j) {
-        const int kb0 = j * AKB, sl = j & 1;
-        const auto rk = rows_rsrc(kbase, rsk, kb0, AKB);
-        const auto rv = rows_rsrc(vbase, rsk, kb0, AKB);
+    constexpr int NCW = AKB / RPI / NW;   // ... of each
+    static_assert(NCW * NW * RPI == AKB, "every wave copies the same share");
+    int coff[NCW];
 #pragma unroll
-        for (int c = wave; c < NCP; c += NW) {
-            const int cc = c % (NCP / 2), r = RPI * cc + lane / NCH;
-            const int off = (int)((r * rsk + (((lane % NCH) ^ swz(r)) << 3)) * 2);
-            if (c < NCP / 2) bdma16(rk, &lds.k[sl][RPI * cc * DH], off);
-            else bdma16(rv, &lds.v[sl][RPI * cc * DH], off);
-        }
+    for (int c = 0; c < NCW; ++c) {
+        const int r = RPI * (wave + NW * c) + lane / NCH;
+        coff[c] = (int)((r * rsk + (((lane % NCH) ^ swz(r)) << 3)) * 2);
+    }
+    auto issue = [&](int j, auto SLOT) {
+        constexpr int sl = decltype(SLOT)::value;
+        const auto rk = rows_rsrc(kbase, rsk, j * AKB, AKB);
+        const auto rv = rows_rsrc(vbase, rsk, j * AKB, AKB);
+#pragma unroll
+        for (int c = 0; c < NCW; ++c) bdma16(rk, &lds.k[sl][RPI * (wave + NW * c) * DH], coff[c]);
+#pragma unroll
+        for (int c = 0; c < NCW; ++c) bdma16(rv, &lds.v[sl][RPI * (wave + NW * c) * DH], coff[c]);
     };
     // Running softmax per query in log2 units.  m is a reference at most RESLACK below
     // the largest scaled score seen (it moves only when a block exceeds it by more:
@@ -2456,7 +2493,7 @@ __global__ __launch_bounds__(NT_ATT / QT) __attribute__((amdgpu_waves_per_eu(4 /
         constexpr int SL = decltype(SLOT)::value;
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // this wave's copies of block j
         lds_barrier();                                       // everyone's; slot (j + 1) & 1 no longer read
-        if (j + 1 < nkb) issue(j + 1);
+        if (j + 1 < nkb) issue(j + 1, Ic<1 - SL>{});
         const int kb0 = j * AKB;
         if (kb0 > qw + 16 * QT - 1) return;   // every key of the block follows this wave's queries
         const bf16_t* sk = lds.k[SL];
@@ -2542,7 +2579,7 @@ __global__ __launch_bounds__(NT_ATT / QT) __attribute__((amdgpu_waves_per_eu(4 /
             }
         }
     };
-    if (nkb > 0) issue(0);
+    if (nkb > 0) issue(0, Ic<0>{});
     for (int j = 0; j < nkb; j += 2) {
         block(j, Ic<0>{});
         if (j + 1 < nkb) block(j + 1, Ic<1>{});
@@ -2955,6 +2992,11 @@ void launch_attention(AttnParams a, hipStream_t st) {
     // product; they pay at d = 128 when the grid gives every CU several workgroups
     // (10k 16-head prompt: 546-554 against 578 us; 2k: 57.6 against 49 us)
     const long wgs = (long)a.nqb * a.B * a.H;
+    // Packed prompts, more workgroups than the CUs hold at once: the longest blocks first, whichever prompt
+    // they belong to, so that the last ones to start are short (8 prompts of 512 to 4096 tokens, 16 heads of
+    // 128: 257 us sequence by sequence, 250 so).  A grid that is resident at once gains nothing and
+    // the search costs each workgroup about a microsecond (3 prompts of 100 to 3000 tokens: 72.9 and 74 us).
+    a.longest_first = a.n_seq > 0 && a.n_seq <= 64 && wgs >= 4 * stream_cus(st);
     if constexpr (DH == 128) {
         if (wgs >= 4 * stream_cus(st)) {
             hipLaunchKernelGGL((k_attn_causal<DH, 2>), dim3((unsigned)wgs), dim3(NT_ATT / 2), 0, st, a);

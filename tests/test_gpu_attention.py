@@ -149,3 +149,24 @@ def test_attention_packed_sequences(d, H, Hkv):
             worst = max(worst, _rel(got[:, s0:s1], ref))
     print("  max rel err o=%.3e" % worst, flush=True)
     assert worst < TOL
+
+
+@pytest.mark.parametrize("n,clamped", [(64, False), (65, False), (5, True)])
+def test_attention_packed_block_order(n, clamped):
+    """Large packed grids take the blocks of up to 64 sequences longest first and those of more sequence by
+    sequence; offsets outside the contract are clamped into a nondecreasing partition of [0, T] either way."""
+    H, Hkv, d, T = 64, 8, 128, 2400
+    if clamped:
+        cu = np.array([0, 700, 300, 5000, -3, 2400], dtype=np.int32)
+    else:
+        cu = np.concatenate([[0], np.sort(np.random.default_rng(n).integers(0, T + 1, n - 1)), [T]]).astype(np.int32)
+    ends = np.minimum(np.maximum.accumulate(np.maximum(cu, 0)), T)
+    print("case: packed order n=%d offsets %s" % (n, cu[:8]), flush=True)
+    assert ((T + 127) // 128 + n) * H >= _wgs_for_two_tiles()
+    x = inputs.make_attention(1, T, H, Hkv, d, seed=760 + n)
+    o = gdn.gdn_attention_prefill(x["q"].cuda(), x["k"].cuda(), x["v"].cuda(), cu_seqlens=torch.from_numpy(cu).cuda())
+    torch.cuda.synchronize()
+    got, (q, k, v) = f64(o), (f64(x[t]) for t in ("q", "k", "v"))
+    for s0, s1 in zip(ends[:-1], ends[1:]):
+        if s1 > s0:
+            assert _rel(got[:, s0:s1], att.causal_attention(q[:, s0:s1], k[:, s0:s1], v[:, s0:s1], 1.0 / d ** 0.5)) < TOL
