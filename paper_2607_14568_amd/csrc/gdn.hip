@@ -1944,17 +1944,30 @@ __global__ __launch_bounds__(NT_CHAIN) __attribute__((amdgpu_waves_per_eu(1, 2))
 // ------------------------------------------------------------------ decode
 // One token per sequence.  LPR lanes hold one state row as float4s; rows of S
 // evolve independently: s_j <- alpha (s_j - beta (s_j.k) k) + beta v_j k.
-template <typename IO, int DK>
+// Bound by memory for a batch (the state in and out) and by its chain of dependent
+// loads and lane sums for a few sequences, so a thread issues the loads of all its NP
+// rows before it uses any: 128 sequences of 16 heads 49 -> 45 us (6.0 TB/s), 64
+// sequences 26 -> 24.6, one sequence 5.7 -> 5.1 (the kernel alone).  One row per thread
+// on four times the workgroups: 74 and 30.5 us, k and q read again by each.
+template <typename IO, int DK, int NP>
 __global__ __launch_bounds__(NT) void k_decode_step(const IO* __restrict__ q, const IO* __restrict__ k,
                                                     const IO* __restrict__ v, const float* __restrict__ g,
                                                     const float* __restrict__ beta, float* __restrict__ S,
-                                                    IO* __restrict__ o, int H, int HK, int DV, int rows_per_wg,
-                                                    float scale, int pre) {
+                                                    IO* __restrict__ o, int H, int HK, int DV, float scale, int pre) {
     constexpr int LPR = DK / 4;        // lanes per row
     constexpr int RPP = NT / LPR;      // rows per pass of the workgroup
     const int bh = blockIdx.y;                                 // sequence * H + head
     const long bk = (long)(bh / H) * HK + (bh % H) / (H / HK);   // its key row: key head h / (H / HK)
     const int tid = threadIdx.x, sub = tid % LPR;
+    const int r0 = blockIdx.x * (NP * RPP) + tid / LPR;   // rows r0 + RPP i; DV is a multiple of NP RPP
+    float4* const rows = reinterpret_cast<float4*>(S + ((long)bh * DV + r0) * DK) + sub;
+    float4 st[NP];
+    float vr[NP];
+#pragma unroll
+    for (int i = 0; i < NP; ++i) {
+        st[i] = rows[(long)i * RPP * LPR];
+        vr[i] = to_f(v[(long)bh * DV + r0 + RPP * i]);
+    }
     float kv[4], qv[4];
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
@@ -1979,25 +1992,22 @@ __global__ __launch_bounds__(NT) void k_decode_step(const IO* __restrict__ q, co
     for (int e = 0; e < 4; ++e) qv[e] *= sq;
     const float a = expf((pre & PRE_GATES) ? gate_g(g[bh]) : g[bh]);
     const float b = (pre & PRE_GATES) ? gate_beta(beta[bh]) : beta[bh];
-    const int r0 = blockIdx.x * rows_per_wg;
-    const int r1 = min(r0 + rows_per_wg, DV);
-    for (int r = r0 + tid / LPR; r < r1; r += RPP) {
-        float4* rowp = reinterpret_cast<float4*>(S + ((long)bh * DV + r) * DK) + sub;
-        float4 sv = *rowp;
+#pragma unroll
+    for (int i = 0; i < NP; ++i) {
+        float4 sv = st[i];
         float sk = sv.x * kv[0] + sv.y * kv[1] + sv.z * kv[2] + sv.w * kv[3];
 #pragma unroll
         for (int m = LPR / 2; m >= 1; m >>= 1) sk += __shfl_xor(sk, m, 64);
-        const float vj = to_f(v[(long)bh * DV + r]);
-        const float cb = b * sk, wv = b * vj;
+        const float cb = b * sk, wv = b * vr[i];
         sv.x = a * (sv.x - cb * kv[0]) + wv * kv[0];
         sv.y = a * (sv.y - cb * kv[1]) + wv * kv[1];
         sv.z = a * (sv.z - cb * kv[2]) + wv * kv[2];
         sv.w = a * (sv.w - cb * kv[3]) + wv * kv[3];
-        *rowp = sv;
+        rows[(long)i * RPP * LPR] = sv;
         float oj = sv.x * qv[0] + sv.y * qv[1] + sv.z * qv[2] + sv.w * qv[3];
 #pragma unroll
         for (int m = LPR / 2; m >= 1; m >>= 1) oj += __shfl_xor(oj, m, 64);
-        if (sub == 0) o[(long)bh * DV + r] = from_f<IO>(oj);
+        if (sub == 0) o[(long)bh * DV + r0 + RPP * i] = from_f<IO>(oj);
     }
 }
 
@@ -2980,10 +2990,9 @@ void launch_wide(Params p, WideParams w, hipStream_t st) {
 template <typename IO, int DK>
 void launch_decode(const void* q, const void* k, const void* v, const float* g, const float* beta,
                    float* S, void* o, int B, int H, int HK, int dv, float scale, int pre, hipStream_t st) {
-    const int rows_per_wg = 32;
-    dim3 grid((dv + rows_per_wg - 1) / rows_per_wg, B * H);
-    hipLaunchKernelGGL((k_decode_step<IO, DK>), grid, dim3(NT), 0, st, (const IO*)q, (const IO*)k,
-                       (const IO*)v, g, beta, S, (IO*)o, H, HK, dv, rows_per_wg, scale, pre);
+    constexpr int ROWS = 32, RPP = NT / (DK / 4);   // rows per workgroup, and of one pass over its threads
+    hipLaunchKernelGGL((k_decode_step<IO, DK, ROWS / RPP>), dim3(dv / ROWS, B * H), dim3(NT), 0, st, (const IO*)q, (const IO*)k,
+                       (const IO*)v, g, beta, S, (IO*)o, H, HK, dv, scale, pre);
 }
 
 template <int DH>
