@@ -139,6 +139,8 @@ def gdn_chunk_prefill_plan(B, T, H, dk, dv, n_seqs=0, io_dtype=GDN_BF16, flags=0
 
 
 def _dev(t, name, dtype=None):
+    if isinstance(t, torch.Tensor) and t.is_cuda and (dtype is None or t.dtype is dtype) and t.is_contiguous():
+        return t
     if not isinstance(t, torch.Tensor) or not t.is_cuda:
         raise TypeError("%s must be a CUDA (HIP) tensor" % name)
     if not t.is_contiguous():
@@ -149,11 +151,18 @@ def _dev(t, name, dtype=None):
 
 
 def _ptr(t):
-    return None if t is None else ctypes.c_void_p(t.data_ptr())
+    return None if t is None else t.data_ptr()   # (ctypes converts the integer by the declared argument type)
+
+
+# The raw handle of the current stream: a call of a few microseconds' work would otherwise spend a tenth of them on
+# building a torch.cuda.Stream object around it.
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
 
 
 def _stream(device):
-    return ctypes.c_void_p(torch.cuda.current_stream(device).cuda_stream)
+    if _raw_stream is not None and device.index is not None:
+        return _raw_stream(device.index)
+    return torch.cuda.current_stream(device).cuda_stream
 
 
 def _prefill_args(q, k, v, g, beta, S0, chunk, cu_seqlens, o, S_T, store_state, workspace, grouped=False, flags=0,
@@ -338,8 +347,8 @@ def _decode(q, k, v, g, beta, S, scale, o, grouped, flags=None):
     B, HK, dk = q.shape
     H = v.shape[1] if grouped else HK
     dv = v.shape[-1]
-    if k.shape != q.shape or tuple(v.shape[:2]) != (B, H) or tuple(g.shape) != (B, H) \
-            or beta.shape != g.shape or tuple(S.shape) != (B, H, dv, dk):
+    if k.shape != q.shape or v.shape[:2] != (B, H) or g.shape != (B, H) or beta.shape != g.shape \
+            or S.shape != (B, H, dv, dk):
         raise ValueError("inconsistent decode shapes")
     if o is None:
         o = torch.empty_like(v)
