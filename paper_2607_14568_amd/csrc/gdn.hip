@@ -1945,10 +1945,13 @@ __global__ __launch_bounds__(NT_CHAIN) __attribute__((amdgpu_waves_per_eu(1, 2))
 // One token per sequence.  LPR lanes hold one state row as float4s; rows of S
 // evolve independently: s_j <- alpha (s_j - beta (s_j.k) k) + beta v_j k.
 // Bound by memory for a batch (the state in and out) and by its chain of dependent
-// loads and lane sums for a few sequences, so a thread issues the loads of all its NP
-// rows before it uses any: 128 sequences of 16 heads 49 -> 45 us (6.0 TB/s), 64
-// sequences 26 -> 24.6, one sequence 5.7 -> 5.1 (the kernel alone).  One row per thread
-// on four times the workgroups: 74 and 30.5 us, k and q read again by each.
+// loads and lane sums for a few sequences, so a thread asks for its first row before
+// k, q and the gates are used and for each next of its NP rows before it works on one:
+// 16 heads, fp32 io, states not in a cache: 128 sequences 48.7 -> 45.0 us (6.0 TB/s), 64
+// 26.3 -> 24.5, 29 12.9 -> 11.9 (in the cache 22.0 -> 21.6 for 64); 512 stay at 202 (5.4
+// TB/s).  All rows asked for at once are as fast from memory but 3 % slower from the
+// cache; one row per thread on four times the workgroups reads k and q as often
+// again (64 sequences 30.5).
 template <typename IO, int DK, int NP>
 __global__ __launch_bounds__(NT) void k_decode_step(const IO* __restrict__ q, const IO* __restrict__ k,
                                                     const IO* __restrict__ v, const float* __restrict__ g,
@@ -1961,13 +1964,8 @@ __global__ __launch_bounds__(NT) void k_decode_step(const IO* __restrict__ q, co
     const int tid = threadIdx.x, sub = tid % LPR;
     const int r0 = blockIdx.x * (NP * RPP) + tid / LPR;   // rows r0 + RPP i; DV is a multiple of NP RPP
     float4* const rows = reinterpret_cast<float4*>(S + ((long)bh * DV + r0) * DK) + sub;
-    float4 st[NP];
-    float vr[NP];
-#pragma unroll
-    for (int i = 0; i < NP; ++i) {
-        st[i] = rows[(long)i * RPP * LPR];
-        vr[i] = to_f(v[(long)bh * DV + r0 + RPP * i]);
-    }
+    float4 next = rows[0];
+    float vnext = to_f(v[(long)bh * DV + r0]);
     float kv[4], qv[4];
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
@@ -1994,11 +1992,16 @@ __global__ __launch_bounds__(NT) void k_decode_step(const IO* __restrict__ q, co
     const float b = (pre & PRE_GATES) ? gate_beta(beta[bh]) : beta[bh];
 #pragma unroll
     for (int i = 0; i < NP; ++i) {
-        float4 sv = st[i];
+        float4 sv = next;
+        const float vj = vnext;
+        if (i + 1 < NP) {
+            next = rows[(long)(i + 1) * RPP * LPR];
+            vnext = to_f(v[(long)bh * DV + r0 + RPP * (i + 1)]);
+        }
         float sk = sv.x * kv[0] + sv.y * kv[1] + sv.z * kv[2] + sv.w * kv[3];
 #pragma unroll
         for (int m = LPR / 2; m >= 1; m >>= 1) sk += __shfl_xor(sk, m, 64);
-        const float cb = b * sk, wv = b * vr[i];
+        const float cb = b * sk, wv = b * vj;
         sv.x = a * (sv.x - cb * kv[0]) + wv * kv[0];
         sv.y = a * (sv.y - cb * kv[1]) + wv * kv[1];
         sv.z = a * (sv.z - cb * kv[2]) + wv * kv[2];
