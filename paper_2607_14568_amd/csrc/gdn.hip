@@ -2820,24 +2820,29 @@ int plan_form(int flags) {
 
 // Time model of the sequential and narrow segmented forms (microseconds), fitted
 // to timings at dk = dv = 128 on a 256-CU MI355X.  The sequential form costs a
-// fixed start and one chain step per chunk.  The segmented form costs a fixed
+// fixed start, one chain step per chunk and a part per token and head.  The segmented form costs a fixed
 // part (its launches, the chunk terms' start), a part per token and head (chunk
 // terms, the output pass), one chain step per chunk of a segment and one scan
 // step per segment.  A chain that needs more workgroups than CUs (one per CU:
 // its LDS) runs in rounds.
 struct SegCost {
-    double seq_fixed, chunk, seg_fixed, per_token_head, per_segment;
+    double seq_fixed, chunk, seq_per_token_head, seg_fixed, per_token_head, per_segment;
 };
-constexpr SegCost COST_BF16 = {17.0, 0.73, 28.5, 3.6e-4, 1.4};
-constexpr SegCost COST_F32 = {15.0, 2.0, 30.0, 5.0e-4, 2.0};
+// Both sides measured over T = 1024 .. 10240 and H = 1 .. 16 (one prompt; us, sequential and the best
+// split): bf16 T = 2048 H = 1 36 and 38, T = 4096 H = 1, 4, 8 57 and 45, 59 and 48, 60.5 and 60,
+// T = 10240 H = 2 123 and 56; fp32 T = 2048 H = 1, 4 63 and 68, 65 and 70, T = 4096 H = 1, 4 111 and
+// 78, 112 and 83.5, T = 10240 H = 2, 8 257 and 103, 282 and 230.
+constexpr SegCost COST_BF16 = {13.0, 0.70, 5.0e-5, 27.5, 3.6e-4, 1.2};
+constexpr SegCost COST_F32 = {15.0, 1.47, 4.0e-4, 46.0, 5.0e-4, 2.2};
 // The wide form (dense bf16, 16 segments, every pass one workgroup per
 // (sequence, segment, head)): a fixed part (four launches, each pass's first
 // loads) and a cost per chunk of a sequence that grows with the units it runs
-// beside, from timings at T = 2048..10240 and B H = 1..16.
+// beside, from timings at T = 1024..10240 and B H = 4..16 (T = 10240, H = 4, 8, 16: 93, 102 and 128 us
+// against 73, 107 and 131 for the better of the other two).
 struct WideCost {
     double fixed, chunk, chunk_per_unit;
 };
-constexpr WideCost COST_WIDE = {46.0, 0.30, 0.019};
+constexpr WideCost COST_WIDE = {42.0, 0.205, 0.021};
 
 SegPlan split_plan(int form, int nc, int P) {
     SegPlan x;
@@ -2878,9 +2883,9 @@ SegPlan choose_plan(int B, int T, int H, int dk, int dv, int n_seqs, int io, int
     if (cus <= 0) return SegPlan{};
     const SegCost& k = io == GDN_BF16 ? COST_BF16 : COST_F32;
     auto rounds = [&](long wgs) { return (double)((wgs + cus - 1) / cus); };
-    const double t_seq = k.seq_fixed + k.chunk * nc * rounds((long)B * H * (dv / SL));
+    const double t_seq = k.seq_fixed + k.chunk * nc * rounds((long)B * H * (dv / SL)) + k.seq_per_token_head * B * H * (double)T;
     SegPlan best_plan;
-    double best = form_req == FORM_SEG ? 1e300 : 0.9 * t_seq;   // splitting by itself must win by a margin
+    double best = form_req == FORM_SEG ? 1e300 : 0.95 * t_seq;   // splitting by itself must win by a margin
     for (int P = 2; P <= std::min(SEG_AUTO_MAX, nc); ++P) {
         const SegPlan x = split_plan(FORM_SEG, nc, P);
         if (x.P != P) continue;
