@@ -358,6 +358,9 @@ template <int AUX = 0> __device__ __forceinline__ void bstore4(float v, __amdgpu
 // Workgroup barrier ordering LDS traffic only: the wave's own LDS operations
 // complete, the compiler moves no memory access across it, and -- unlike
 // __syncthreads() -- it does not wait for outstanding global loads or stores.
+// The wait is what keeps a wave's reads ahead of another wave's writes after the
+// barrier: what uses the values read is register arithmetic, which the compiler
+// may move past it.  So no barrier is written without it.
 __device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
 
 // x = hi + lo with hi = bf16(x), lo = bf16(x - hi): a product of two such pairs
@@ -735,8 +738,8 @@ __device__ __forceinline__ void state_chain_f32(const Params& p, const int bid, 
             asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
             lds_barrier();   // A_c
             if (c + 1 < nc) issue(c + 1);
-            asm volatile("s_barrier" ::: "memory");   // B_c
-            asm volatile("s_barrier" ::: "memory");   // C_c
+            lds_barrier();   // B_c
+            lds_barrier();   // C_c
         }
         return;
     }
@@ -800,9 +803,9 @@ __device__ __forceinline__ void state_chain_f32(const Params& p, const int bid, 
         };
         if (nc > 0) {
             load(0);
-            lds_barrier();                            // A_0
-            asm volatile("s_barrier" ::: "memory");   // B_0
-            asm volatile("s_barrier" ::: "memory");   // C_0
+            lds_barrier();   // A_0
+            lds_barrier();   // B_0
+            lds_barrier();   // C_0
         }
         for (int c = 1; c < nc; ++c) {   // step c: the outputs of chunk c - 1
             lds_barrier();   // A_c
@@ -810,7 +813,7 @@ __device__ __forceinline__ void state_chain_f32(const Params& p, const int bid, 
             lds_barrier();   // B_c
             read_s(c - 1);   // S_{c-1}: overwritten after C_c
             qs();
-            asm volatile("s_barrier" ::: "memory");   // C_c
+            lds_barrier();   // C_c: its wait holds the reads of S_{c-1} back; the products of qs may sink below it
             pu_store(c - 1);
             load(c);
         }
