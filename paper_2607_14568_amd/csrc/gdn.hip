@@ -136,13 +136,13 @@ struct Params {
     int wait_bound;      // fused bf16 launch: most flag polls of one chain workgroup in the call
     int withhold;        // fused bf16 launch: chunk terms publish nothing (GDN_TEST_WITHHOLD)
     int npw;             // fused bf16 launch: chunk-terms workgroups ahead of the chain workgroups
+    int term_waves;      // ... and the waves of each that form chunk terms
     int xcd_items;       // fused bf16 launch: chunk-terms items assigned by XCD (dense, 8 | H, 8 | npw)
     float scale;
     int pre;             // PRE_L2 | PRE_GATES
     float* snaps;        // state snapshots [n_seq, n_snap, H, DV, dk] (the SNAP kernels only)
     int snap_every;      // ... after every snap_every chunks of a sequence, strictly inside it
     int n_snap;
-    int term_waves;      // ... and the waves of each that form chunk terms
 };
 
 // Entry i of a sequence table, read where every lane of the wave reads the same
@@ -154,23 +154,20 @@ __device__ __forceinline__ int tab(const int32_t* a, long i) { return __builtin_
 __device__ __forceinline__ int seq_at_rank(const Params& p, int r) { return p.ragged ? tab(p.seq_perm, r) : r; }
 
 // Work item k of the chunk terms in the order the chains consume them: chunk
-// index within its sequence, then sequence rank, then head.
-__device__ __forceinline__ long item_slot(const Params& p, long k) {
-    const int H = p.H;
-    int c, r;
+// index within its sequence, then sequence rank, then head, over the hu heads
+// h0, h0 + hs, ... (ragged: all heads).  Items are fewer than 2^31: each takes
+// more than 8 KB of the workspace.
+__device__ __forceinline__ int item_slot(const Params& p, int k, int hu, int h0, int hs) {
+    const int h = h0 + hs * (k % hu), kr = k / hu;   // kr: chunk index and rank
     if (p.ragged) {
-        int lo = 0, hi = p.cpt;   // largest c with cprefix[c] * H <= k
+        int lo = 0, hi = p.cpt;   // largest c with cprefix[c] <= kr
         while (hi - lo > 1) {
             const int mid = (lo + hi) >> 1;
-            if ((long)tab(p.cprefix, mid) * H <= k) lo = mid; else hi = mid;
+            if (tab(p.cprefix, mid) <= kr) lo = mid; else hi = mid;
         }
-        c = lo;
-        r = (int)((k - (long)tab(p.cprefix, c) * H) / H);
-        return ((long)tab(p.chunk_off, tab(p.seq_perm, r)) + c) * H + (int)(k % H);
+        return (tab(p.chunk_off, tab(p.seq_perm, kr - tab(p.cprefix, lo))) + lo) * p.H + h;
     }
-    c = (int)(k / ((long)p.n_seq * H));
-    r = (int)((k / H) % p.n_seq);
-    return ((long)r * p.NC + c) * H + (int)(k % H);
+    return (kr % p.n_seq * p.NC + kr / p.n_seq) * p.H + h;
 }
 
 __device__ __forceinline__ void seq_info(const Params& p, int s, long& start, int& len, int& cbase) {
@@ -1633,12 +1630,12 @@ __device__ __forceinline__ void wave_lds_fence() { asm volatile("" ::: "memory")
 // copied into vsink (1 KB of LDS nobody reads) so that they wait in L2 for the
 // chain.
 template <int DK, bool FUSED, bool NORM>
-__device__ __forceinline__ void chunk_terms_bf16(const Params& p, const long gi, TermsLds& lds, const int lane,
+__device__ __forceinline__ void chunk_terms_bf16(const Params& p, const int gi, TermsLds& lds, const int lane,
                                                  bf16_t* vsink = nullptr) {
     constexpr int NKD = DK / 32;
     constexpr int AUX = FUSED ? 17 : 0;
     const int H = p.H;
-    const int gc = (int)(gi / H), h = (int)(gi % H);
+    const int gc = gi / H, h = gi % H;
     int s;
     if (p.ragged) {
         if (gc >= tab(p.chunk_off, p.n_seq)) return;
@@ -1907,6 +1904,21 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2, 2))) void
 // Q and V rows gone from them, and crowd its loads: with 1, 2, 3, 4 and 8 waves in each
 // of 128 workgroups the call of 10240 tokens and 16 heads took 160, 131.7, 140, 145 and 154 us.
 constexpr int TERM_WAVES_MAX = NT_CHAIN / 64, TERM_WAVES_ALL = 256;
+
+// The kernel's only parameter, read anew from the kernel's argument segment: nothing read through the
+// reference is held in registers from before this point.
+__device__ __forceinline__ const Params& fresh_params() {
+    auto p = (const __attribute__((address_space(4))) Params*)__builtin_amdgcn_kernarg_segment_ptr();
+    asm volatile("" : "+s"(p));
+    return *(const Params*)p;
+}
+
+// Registers: an item's body takes nearly all 256 vector registers, and either role most of the scalar
+// ones.  So the body stands at one place, the lane index is renewed for each item (its per-lane addresses
+// are then formed again, not kept), and each role reads the parameters for itself, the chunk terms once
+// per item.  Without this the kernel spilled 10 to 20 vector registers to scratch and the chain moved up
+// to 470 scalar values through vector lanes: 10240 tokens, 16 heads of 128 132.5 us, 126.8 with it;
+// 4000 tokens, 8 heads 58.9 and 56.1; 3001 tokens with transforms and snapshots 53.5 and 50.7.
 template <int DK, bool SNAP = false, bool NORM = false>
 __global__ __launch_bounds__(NT_CHAIN) __attribute__((amdgpu_waves_per_eu(1, 2))) void k_prefill_fused_bf16(Params p) {
     __shared__ union Lds {
@@ -1918,29 +1930,25 @@ __global__ __launch_bounds__(NT_CHAIN) __attribute__((amdgpu_waves_per_eu(1, 2))
         } t[TERM_WAVES_MAX];
     } lds;
     if ((int)blockIdx.x < p.npw) {
-        const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+        const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+        int lane = threadIdx.x & 63;
         if (wave >= p.term_waves) return;
         auto& my = lds.t[wave];
-        if (p.xcd_items) {
-            // Dispatch deals workgroups to the 8 XCDs round-robin, so chain
-            // workgroups of head h sit on XCD (npw + h) % 8.  Workgroup b forms
-            // the items of heads h = (b - npw) mod 8 (+ 8 u), in chunk order, on
-            // the XCD whose L2 then serves those chains.
-            const int H = p.H, hu = H / 8, q = blockIdx.x / 8, nq = p.npw / 8;
-            const int h0 = ((int)(blockIdx.x % 8) - p.npw % 8 + 8) % 8;
-            const long items = (long)p.NC * p.n_seq * hu;   // per XCD
-            for (long j = (long)wave * nq + q; j < items; j += (long)p.term_waves * nq) {
-                const int c = (int)(j / ((long)p.n_seq * hu)), r = (int)((j / hu) % p.n_seq), u = (int)(j % hu);
-                chunk_terms_bf16<DK, true, NORM>(p, ((long)r * p.NC + c) * H + h0 + 8 * u, my.t, lane, my.vsink);
-            }
-        } else {
-            const long items = (long)(p.ragged ? tab(p.chunk_off, p.n_seq) : p.n_seq * p.NC) * p.H;
-            for (long k = (long)wave * p.npw + blockIdx.x; k < items; k += (long)p.term_waves * p.npw)
-                chunk_terms_bf16<DK, true, NORM>(p, item_slot(p, k), my.t, lane, my.vsink);
+        // Dispatch deals workgroups to the 8 XCDs round-robin, so chain workgroups of head h
+        // sit on XCD (npw + h) % 8.  With xcd_items workgroup b forms the items of heads
+        // h = (b - npw) mod 8 (+ 8 u), in chunk order, on the XCD whose L2 then serves those chains.
+        const int xs = p.xcd_items ? 8 : 1, hu = p.H / xs, nq = p.npw / xs;
+        const int h0 = p.xcd_items ? ((int)(blockIdx.x % 8) - p.npw % 8 + 8) % 8 : 0;
+        const int items = (p.ragged ? tab(p.chunk_off, p.n_seq) : p.n_seq * p.NC) * hu;
+        for (int k = wave * nq + (int)blockIdx.x / xs; k < items; k += p.term_waves * nq) {
+            asm volatile("" : "+v"(lane));
+            const Params& pi = fresh_params();
+            chunk_terms_bf16<DK, true, NORM>(pi, item_slot(pi, k, hu, h0, xs), my.t, lane, my.vsink);
         }
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // the copies into vsink
     } else {
-        state_chain_bf16<DK, 1, true, false, SNAP, NORM>(p, blockIdx.x - p.npw, lds.c);
+        const Params& pc = fresh_params();
+        state_chain_bf16<DK, 1, true, false, SNAP, NORM>(pc, blockIdx.x - pc.npw, lds.c);
     }
 }
 
