@@ -1956,14 +1956,16 @@ __global__ __launch_bounds__(NT_CHAIN) __attribute__((amdgpu_waves_per_eu(1, 2))
 // One token per sequence.  LPR lanes hold one state row as float4s; rows of S
 // evolve independently: s_j <- alpha (s_j - beta (s_j.k) k) + beta v_j k.
 // Bound by memory for a batch (the state in and out) and by its chain of dependent
-// loads and lane sums for a few sequences, so a thread asks for its first row before
+// loads and lane sums for a few sequences.  AHEAD: a thread asks for its first row before
 // k, q and the gates are used and for each next of its NP rows before it works on one:
-// 16 heads, fp32 io, states not in a cache: 128 sequences 48.7 -> 45.0 us (6.0 TB/s), 64
-// 26.3 -> 24.5, 29 12.9 -> 11.9 (in the cache 22.0 -> 21.6 for 64); 512 stay at 202 (5.4
-// TB/s).  All rows asked for at once are as fast from memory but 3 % slower from the
-// cache; one row per thread on four times the workgroups reads k and q as often
-// again (64 sequences 30.5).
-template <typename IO, int DK, int NP>
+// 16 heads, fp32 io, states not in a cache: 128 sequences 46.6 -> 43.8 us (6.1 TB/s), 64
+// 26.4 -> 24.4, 29 12.9 -> 11.9 (in the cache 22.0 -> 21.6 for 64).  All rows asked for at
+// once are as fast from memory but 3 % slower from the cache; one row per thread on four
+// times the workgroups reads k and q as often again (64 sequences 30.5).
+// Not AHEAD: each row when it is worked on.  States that do not fit the last-level cache
+// then stream better, most with grouped heads and transforms: 512 sequences, bf16 io, 4 key
+// heads 201.3 -> 192.1 us, 400 158.0 -> 154.5; plain fp32 512 204.5 -> 203.4.
+template <typename IO, int DK, int NP, bool AHEAD>
 __global__ __launch_bounds__(NT) void k_decode_step(const IO* __restrict__ q, const IO* __restrict__ k,
                                                     const IO* __restrict__ v, const float* __restrict__ g,
                                                     const float* __restrict__ beta, float* __restrict__ S,
@@ -1975,8 +1977,14 @@ __global__ __launch_bounds__(NT) void k_decode_step(const IO* __restrict__ q, co
     const int tid = threadIdx.x, sub = tid % LPR;
     const int r0 = blockIdx.x * (NP * RPP) + tid / LPR;   // rows r0 + RPP i; DV is a multiple of NP RPP
     float4* const rows = reinterpret_cast<float4*>(S + ((long)bh * DV + r0) * DK) + sub;
-    float4 next = rows[0];
-    float vnext = to_f(v[(long)bh * DV + r0]);
+    auto row = [&](int i) -> float4& { return rows[(long)i * RPP * LPR]; };
+    auto value = [&](int i) { return to_f(v[(long)bh * DV + r0 + RPP * i]); };
+    float4 next;
+    float vnext;
+    if constexpr (AHEAD) {
+        next = row(0);
+        vnext = value(0);
+    }
     float kv[4], qv[4];
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
@@ -2001,23 +2009,26 @@ __global__ __launch_bounds__(NT) void k_decode_step(const IO* __restrict__ q, co
     for (int e = 0; e < 4; ++e) qv[e] *= sq;
     const float a = expf((pre & PRE_GATES) ? gate_g(g[bh]) : g[bh]);
     const float b = (pre & PRE_GATES) ? gate_beta(beta[bh]) : beta[bh];
-#pragma unroll
+#pragma unroll (AHEAD ? NP : 1)
     for (int i = 0; i < NP; ++i) {
-        float4 sv = next;
-        const float vj = vnext;
-        if (i + 1 < NP) {
-            next = rows[(long)(i + 1) * RPP * LPR];
-            vnext = to_f(v[(long)bh * DV + r0 + RPP * (i + 1)]);
+        float4 sv;
+        if constexpr (AHEAD) {
+            sv = next;
+            if (i + 1 < NP) next = row(i + 1);
+        } else {
+            sv = row(i);
         }
         float sk = sv.x * kv[0] + sv.y * kv[1] + sv.z * kv[2] + sv.w * kv[3];
 #pragma unroll
         for (int m = LPR / 2; m >= 1; m >>= 1) sk += __shfl_xor(sk, m, 64);
+        const float vj = AHEAD ? vnext : value(i);
+        if (AHEAD && i + 1 < NP) vnext = value(i + 1);
         const float cb = b * sk, wv = b * vj;
         sv.x = a * (sv.x - cb * kv[0]) + wv * kv[0];
         sv.y = a * (sv.y - cb * kv[1]) + wv * kv[1];
         sv.z = a * (sv.z - cb * kv[2]) + wv * kv[2];
         sv.w = a * (sv.w - cb * kv[3]) + wv * kv[3];
-        rows[(long)i * RPP * LPR] = sv;
+        row(i) = sv;
         float oj = sv.x * qv[0] + sv.y * qv[1] + sv.z * qv[2] + sv.w * qv[3];
 #pragma unroll
         for (int m = LPR / 2; m >= 1; m >>= 1) oj += __shfl_xor(oj, m, 64);
@@ -3010,8 +3021,15 @@ template <typename IO, int DK>
 void launch_decode(const void* q, const void* k, const void* v, const float* g, const float* beta,
                    float* S, void* o, int B, int H, int HK, int dv, float scale, int pre, hipStream_t st) {
     constexpr int ROWS = 32, RPP = NT / (DK / 4);   // rows per workgroup, and of one pass over its threads
-    hipLaunchKernelGGL((k_decode_step<IO, DK, ROWS / RPP>), dim3(dv / ROWS, B * H), dim3(NT), 0, st, (const IO*)q, (const IO*)k,
-                       (const IO*)v, g, beta, S, (IO*)o, H, HK, dv, scale, pre);
+    const auto launch = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, dim3(dv / ROWS, B * H), dim3(NT), 0, st, (const IO*)q, (const IO*)k, (const IO*)v, g, beta, S,
+                           (IO*)o, H, HK, dv, scale, pre);
+    };
+    // rows ahead of their use while the states fit the last-level cache (256 MB); both sides at k_decode_step
+    if ((long)B * H * dv * DK * 4 <= 256L << 20)
+        launch(k_decode_step<IO, DK, ROWS / RPP, true>);
+    else
+        launch(k_decode_step<IO, DK, ROWS / RPP, false>);
 }
 
 template <int DH>

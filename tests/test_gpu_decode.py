@@ -59,3 +59,31 @@ def test_decode_b512_workload():
     """512 sequences x 16 heads (537 MB of state, past the Infinity Cache): 3 steps, every output compared."""
     print("case: decode_b512_f32", flush=True)
     _replay(inputs.make_workload("decode_b512_f32"), 3, 2e-4)
+
+
+@pytest.mark.parametrize("dk,dv", [(64, 64), (128, 128), (64, 128), (128, 64)])
+@pytest.mark.parametrize("io,raw", [("f32", False), ("bf16", True)])
+def test_decode_past_the_cache(io, raw, dk, dv):
+    """The smallest batch whose states exceed 256 MB, where each row is loaded when it is worked on; the
+    first, middle and last sequences against the oracle."""
+    H, HK = 2, 1
+    B = (256 << 20) // (H * dv * dk * 4) + 1
+    print("case: decode past the cache", io, raw, dk, dv, B, flush=True)
+    rng = torch.Generator(device="cuda").manual_seed(dk + 2 * dv)
+    dt = torch.float32 if io == "f32" else torch.bfloat16
+
+    def normal(*shape):
+        return torch.randn(shape, generator=rng, device="cuda")
+
+    q, k, v = normal(B, HK, dk), normal(B, HK, dk), normal(B, H, dv)
+    if not raw:
+        q, k = q / q.norm(dim=-1, keepdim=True), k / k.norm(dim=-1, keepdim=True)
+    q, k, v = q.to(dt), k.to(dt), v.to(dt)
+    g, beta, S = -normal(B, H).abs(), normal(B, H).sigmoid(), 0.05 * normal(B, H, dv, dk)
+    pick = torch.tensor([0, 1, B // 2, B - 2, B - 1])
+    S_in = f64(S[pick])
+    o = gdn.gdn_decode_step_ex(q, k, v, g, beta, S, flags=gdn.GDN_QK_L2NORM | gdn.GDN_GATE_LOGITS if raw else 0)
+    torch.cuda.synchronize()
+    ref = oracle.decode_step_ex(*(f64(t[pick]) for t in (q, k, v, g, beta)), S_in, qk_l2norm=raw, gate_logits=raw)
+    tol = 2e-4 if io == "f32" else 2e-2
+    assert oracle.max_rel_err(f64(o[pick]), ref[0]) < tol and oracle.max_rel_err(f64(S[pick]), ref[1]) < tol
