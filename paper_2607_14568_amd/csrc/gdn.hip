@@ -1898,11 +1898,16 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2, 2))) void
 // the first wave of every workgroup), the rest are chain workgroups.  The
 // chunk-terms workgroups are dispatched first and never wait, so the chain
 // workgroups' waits end whatever number of workgroups the device holds at once.
-// p.term_waves waves form chunk terms in each such workgroup, about 256 in all: enough
-// to stay ahead of the chain (16 heads consume 16 items per 0.74 us; an item takes
-// about 9 us).  More run further ahead than the L2s hold, so the chain finds its K,
-// Q and V rows gone from them, and crowd its loads: with 1, 2, 3, 4 and 8 waves in each
-// of 128 workgroups the call of 10240 tokens and 16 heads took 160, 131.7, 140, 145 and 154 us.
+// p.term_waves waves form chunk terms in each such workgroup: the count that brings all of
+// them nearest to 256, which is 170 to 340 for 64 workgroups and more (fewer take all 8
+// waves each).  That is enough to stay ahead of the chain (16 heads consume 16 items per
+// 0.7 us; an item takes about 9 us).  More run further ahead than the L2s hold, so the
+// chain finds its K, Q and V rows gone from them, and crowd its loads: with 1, 2, 3, 4 and 8
+// waves in each of 128 workgroups the call of 10240 tokens and 16 heads took 160, 131.7, 140,
+// 145 and 154 us; in each of 192, 4000 tokens and 8 heads take 55.4 us with 1 and 56.4 with 2
+// (10240 tokens, 16 heads of 64 104.5 and 107.4); in each of 96, 5 prompts of 1500 tokens and
+// 4 heads 32.7 with 2 and 31.4 with 3.  As many waves in fewer workgroups start later:
+// 300 tokens, 16 heads 16.1 against 15.4.
 constexpr int TERM_WAVES_MAX = NT_CHAIN / 64, TERM_WAVES_ALL = 256;
 
 // The kernel's only parameter, read anew from the kernel's argument segment: nothing read through the
@@ -2800,7 +2805,7 @@ void launch_prefill(Params p, long slots, hipStream_t st) {
             p.npw = (int)std::min(spare, items);
             p.xcd_items = !p.ragged && p.H % 8 == 0 && p.npw >= 8;
             if (p.xcd_items) p.npw &= ~7;
-            p.term_waves = std::max(1, std::min(TERM_WAVES_MAX, (TERM_WAVES_ALL + p.npw - 1) / p.npw));
+            p.term_waves = std::max(1, std::min(TERM_WAVES_MAX, (TERM_WAVES_ALL + p.npw / 2) / p.npw));
             p.epoch = next_epoch();
             hipLaunchKernelGGL((k_prefill_fused_bf16<DK, SNAP, NORM>), dim3((unsigned)(p.npw + nchain)), dim3(NT_CHAIN), 0,
                                st, p);
