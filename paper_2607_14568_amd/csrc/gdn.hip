@@ -2788,21 +2788,26 @@ uint64_t next_epoch() {
     return (epoch_salt() << 32) | (uint32_t)(counter.fetch_add(1, std::memory_order_relaxed) + 1);
 }
 
+// How the bf16 sequential form runs its wgs chain workgroups of 16 state rows (one per CU: their LDS).
+// One launch, the chunk terms formed beside the chain, while the chain leaves a quarter of the CUs free.
+bool one_launch(long wgs, long cus) { return cus - wgs >= 8 && 4 * (cus - wgs) >= cus; }
+// Dense input, otherwise: two groups of 16 rows per workgroup when that saves rounds, which is when one
+// group would need more than one: a chunk step of 32 state rows takes about 1.3 times one of 16.
+bool two_row_groups(long wgs, long cus) { return wgs > cus; }
+
 template <typename IO, int DK, bool SNAP = false, bool NORM = false>
 void launch_prefill(Params p, long slots, hipStream_t st) {
     if (p.ragged)
         hipLaunchKernelGGL(k_ragged_setup, dim3(1), dim3(NSET), 0, st, p.cu, p.n_seq, p.T, p.seq_start,
                            p.seq_len, p.chunk_off, p.seq_perm, p.cprefix, p.cprefix + (p.cpt + 2), p.cpt, CH);
     if constexpr (sizeof(IO) == 2) {
-        // one launch with the chunk terms formed beside the chain when it leaves
-        // a quarter of the compute units free; otherwise the chunk terms first
-        // (three workgroups per CU) and the chain after, longest sequence first
+        // one launch, or the chunk terms first (one-wave workgroups, eight per CU) and the chain
+        // after, longest sequence first
         const long nchain = (long)p.n_seq * p.H * (p.DV / SL);
         const long items = slots * p.H;
         const long cus = stream_cus(st);
-        const long spare = cus - nchain;   // CUs the chain leaves free (one chain workgroup per CU)
-        if (spare >= 8 && 4 * spare >= cus && items > 0) {
-            p.npw = (int)std::min(spare, items);
+        if (one_launch(nchain, cus) && items > 0) {
+            p.npw = (int)std::min(cus - nchain, items);
             p.xcd_items = !p.ragged && p.H % 8 == 0 && p.npw >= 8;
             if (p.xcd_items) p.npw &= ~7;
             p.term_waves = std::max(1, std::min(TERM_WAVES_MAX, (TERM_WAVES_ALL + p.npw / 2) / p.npw));
@@ -2819,15 +2824,14 @@ void launch_prefill(Params p, long slots, hipStream_t st) {
             hipLaunchKernelGGL((k_chunk_terms<DK>), dim3((unsigned)(slots * p.H)), dim3(NT_T32), 0, st, p);
     }
     if constexpr (sizeof(IO) == 2) {
-        // Two row groups per workgroup when that saves rounds: a chunk step of 32 state rows takes
-        // about 1.3 times one of 16 (measured at 16 heads of 128, d = 128, one and two groups: 2 x 4096 tokens,
-        // 256 and 128 workgroups: 85 and 101 us; 3 x 1500 tokens, 384 and 192: 65 and 51; 4 x 1000: 53
-        // and 40; 8 packed prompts, 17481 tokens, 1024 and 512: 213 and 164).  Packed prompts differ in
+        // One and two row groups at 16 heads of 128: 2 x 4096 tokens, 256 and 128 workgroups: 71 and
+        // 84 us; 3 x 1500 tokens, 384 and 192: 58 and 44.5; 4 x 1000: 46 and 35; 5 x 2000: 105 and 95; of
+        // 64: 8 x 1280, 512 and 256: 52 and 42, 4 x 1000, 256 and 128: 24.6 and 27.4; with the input
+        // transforms or snapshots the same way (3 x 1500: 62 and 48, 64 and 52).  Packed prompts differ in
         // length, so their workgroups spread better over the CUs than rounds say (3 prompts of 300 to
-        // 2000 tokens, 384 and 192: 55 and 60 us): there from two workgroups per CU on.
+        // 2000 tokens, 384 and 192: 47 and 52 us): there from two workgroups per CU on.
         const long cus = std::max(1, stream_cus(st)), wgs = (long)p.n_seq * p.H * (p.DV / SL);
-        const auto rounds = [&](long n) { return (double)((n + cus - 1) / cus); };
-        const bool two = p.ragged ? wgs >= 2 * cus : 1.3 * rounds(wgs / 2) < rounds(wgs);
+        const bool two = p.ragged ? wgs >= 2 * cus : two_row_groups(wgs, cus);
         if (two)
             hipLaunchKernelGGL((k_state_chain_bf16<DK, 2, SNAP, NORM>), dim3((unsigned)(wgs / 2)), dim3(NT_CHAIN), 0, st, p);
         else
@@ -2869,21 +2873,37 @@ int plan_form(int flags) {
 struct SegCost {
     double seq_fixed, chunk, seq_per_token_head, seg_fixed, per_token_head, per_segment;
 };
+// The bf16 sequential form as two launches (one_launch): a fixed start, the chunk terms per token and
+// head, and chain steps by its row groups (two_row_groups) and rounds, which take longer once what the
+// chunk terms leave behind has to come from memory (the last-level cache holds 256 MB).  Measured and modelled, us:
+// 2 x 5120 tokens, 16 heads 89 and 90; 3 x 3413 82 and 84; 3 x 8192 252 and 269; 8 x 1280 75 and 73; 8 x 4096 292
+// and 291; 10240 tokens, 32 heads 226 and 229, 40 heads 322 and 319, 64 heads 351 and 361.
+struct TwoLaunchCost {
+    double fixed, per_token_head, step[2], step_cold[2];   // by row groups - 1
+};
+constexpr TwoLaunchCost COST_TWO = {11.0, 1.7e-4, {0.645, 0.84}, {0.45, 0.65}};
+constexpr double COLD_FROM_MB = 220, COLD_FULL_MB = 440;   // bytes of the call's inputs, outputs and chunk terms
 // Both sides measured over T = 1024 .. 10240 and H = 1 .. 16 (one prompt; us, sequential and the best
 // split): bf16 T = 2048 H = 1 36 and 38, T = 4096 H = 1, 4, 8 57 and 45, 59 and 48, 60.5 and 60,
 // T = 10240 H = 2 123 and 56; fp32 T = 2048 H = 1, 4 63 and 68, 65 and 70, T = 4096 H = 1, 4 111 and
-// 78, 112 and 83.5, T = 10240 H = 2, 8 257 and 103, 282 and 230.
+// 78, 112 and 83.5, T = 10240 H = 2, 8 257 and 103, 282 and 230; 3 prompts of 2 heads, T = 6144 and 8192, 168
+// and 218 (5 segments, the choice, 146 and 191; 2 139 and 167; 8 170 and 197), T = 3413 99 and 106.
 constexpr SegCost COST_BF16 = {13.0, 0.70, 5.0e-5, 27.5, 3.6e-4, 1.2};
 constexpr SegCost COST_F32 = {15.0, 1.47, 4.0e-4, 46.0, 5.0e-4, 2.2};
 // The wide form (dense bf16, 16 segments, every pass one workgroup per
 // (sequence, segment, head)): a fixed part (four launches, each pass's first
 // loads) and a cost per chunk of a sequence that grows with the units it runs
 // beside, from timings at T = 1024..10240 and B H = 4..16 (T = 10240, H = 4, 8, 16: 93, 102 and 128 us
-// against 73, 107 and 131 for the better of the other two).
+// against 73, 107 and 131 for the better of the other two; B H = 8, T = 6144 and 8192 76 and 87.5 against
+// 76 and 97 sequential; 3 prompts of 2 heads 76 and 86 against 75 and 96).  Beyond 16 units also what comes
+// from memory, and a pass of more workgroups than CUs runs a second round (wide and sequential: 24 units of 8192
+// tokens 154 and 133; 10240 tokens, 32, 36, 40 and 48 units 203 and 226, 283 and 305, 315 and 322, 363 and 344;
+// 3 x 8192 tokens, 16 heads 293 and 252).
 struct WideCost {
-    double fixed, chunk, chunk_per_unit;
+    double fixed, chunk, chunk_per_unit, per_cold_mb, chunk_per_unit_round;
 };
-constexpr WideCost COST_WIDE = {42.0, 0.205, 0.021};
+constexpr WideCost COST_WIDE = {42.0, 0.205, 0.021, 0.12, 0.009};
+constexpr int WIDE_FIT_UNITS = 16;
 
 SegPlan split_plan(int form, int nc, int P) {
     SegPlan x;
@@ -2924,19 +2944,34 @@ SegPlan choose_plan(int B, int T, int H, int dk, int dv, int n_seqs, int io, int
     if (cus <= 0) return SegPlan{};
     const SegCost& k = io == GDN_BF16 ? COST_BF16 : COST_F32;
     auto rounds = [&](long wgs) { return (double)((wgs + cus - 1) / cus); };
-    const double t_seq = k.seq_fixed + k.chunk * nc * rounds((long)B * H * (dv / SL)) + k.seq_per_token_head * B * H * (double)T;
+    const long wgs = (long)B * H * (dv / SL);
+    const double tokens = (double)B * H * T;
+    const double mb = tokens * (4 * (dk + dv) + 208) * 1e-6;   // bf16: q, k, v, o, gates, and the chunk terms
+    double t_seq = k.seq_fixed + k.chunk * nc * rounds(wgs) + k.seq_per_token_head * tokens;
+    if (io == GDN_BF16 && !one_launch(wgs, cus)) {
+        const int two = two_row_groups(wgs, cus);
+        const double cold = std::min(1.0, std::max(0.0, (mb - COLD_FROM_MB) / (COLD_FULL_MB - COLD_FROM_MB)));
+        t_seq = COST_TWO.fixed + COST_TWO.per_token_head * tokens +
+                nc * rounds(two ? wgs / 2 : wgs) * (COST_TWO.step[two] + COST_TWO.step_cold[two] * cold);
+    }
     SegPlan best_plan;
     double best = form_req == FORM_SEG ? 1e300 : 0.95 * t_seq;   // splitting by itself must win by a margin
     for (int P = 2; P <= std::min(SEG_AUTO_MAX, nc); ++P) {
         const SegPlan x = split_plan(FORM_SEG, nc, P);
         if (x.P != P) continue;
-        const double t = k.seg_fixed + k.per_token_head * B * H * (double)T +
+        const double t = k.seg_fixed + k.per_token_head * tokens +
                          k.chunk * x.L * rounds((long)B * P * H * ((dv + dk) / SL)) + k.per_segment * P;
         if (t < best) { best = t; best_plan = x; }
     }
     if (form_req == FORM_AUTO && wide) {
-        const double t = COST_WIDE.fixed + nc * (COST_WIDE.chunk + COST_WIDE.chunk_per_unit * (double)B * H);
-        if (t < best) best_plan = split_plan(FORM_WIDE, nc, wide_auto_P(B, H, nc));
+        const double units = (double)B * H;
+        const SegPlan x = split_plan(FORM_WIDE, nc, wide_auto_P(B, H, nc));
+        double t = COST_WIDE.fixed + nc * (COST_WIDE.chunk + COST_WIDE.chunk_per_unit * units);
+        if (units > WIDE_FIT_UNITS) {
+            t += COST_WIDE.per_cold_mb * std::max(0.0, mb - COLD_FROM_MB);
+            if (units * x.P > cus) t += COST_WIDE.chunk_per_unit_round * nc * units;
+        }
+        if (t < best) best_plan = x;
     }
     return best_plan;
 }

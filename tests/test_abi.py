@@ -90,6 +90,13 @@ def test_plans_and_workspace():
     assert auto[(bf, 8)] == wsx(1, 10240, 8, 128, 128, 64, 0, bf, WIDE, 0)
     # short bf16 prompts stay sequential (the split's fixed costs outweigh its gain)
     assert ws(1, 2048, 2, 128, 128, 64, 0, bf) == wsx(1, 2048, 2, 128, 128, 64, 0, bf, SEQ, 0)
+    # more chain workgroups than CUs: two row groups each, which the split forms do not beat; a wide pass of
+    # 288 workgroups is two rounds, of 256 one
+    for B, T, H, d in [(3, 8192, 16, 128), (3, 3413, 16, 128), (8, 4096, 16, 128), (1, 10240, 48, 128), (1, 7168, 34, 128),
+                       (1, 10240, 64, 128), (1, 8192, 24, 128), (2, 8192, 16, 128), (5, 8192, 16, 64)]:
+        assert ws(B, T, H, d, d, 64, 0, bf) == wsx(B, T, H, d, d, 64, 0, bf, SEQ, 0), (B, T, H, d)
+    for B, T, H in [(1, 10240, 32), (1, 10240, 36), (1, 16384, 40), (1, 16384, 16), (1, 8192, 8)]:
+        assert ws(B, T, H, 128, 128, 64, 0, bf) == wsx(B, T, H, 128, 128, 64, 0, bf, WIDE, 0), (B, T, H)
     # forced: more segments, more workspace; ragged input never splits
     two = wsx(1, 4096, 2, 128, 128, 64, 0, bf, SEG, 2)
     assert wsx(1, 4096, 2, 128, 128, 64, 0, bf, SEG, 8) > two
