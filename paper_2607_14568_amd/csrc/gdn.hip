@@ -124,6 +124,7 @@ struct Params {
     int32_t* chunk_off;  // [n_seq + 1], first chunk slot of each sequence
     int32_t* seq_perm;   // ragged: sequences by chunk count, longest first
     int32_t* cprefix;    // ragged: [cpt + 1] (sequence, chunk index < c) pair counts
+    int32_t* row_groups; // k_state_chain_packed_bf16: groups of 16 state rows per workgroup (from k_ragged_setup)
     int cpt;             // chunks of the longest possible sequence
     float* wsG;          // [slot][H][GS]: gamma_r = exp(G_r), D_r = exp(G_n - G_r) (times s_k,r with PRE_L2
                          // in fp32 io), and with PRE_L2 gamma_r s_k,r and gamma_r s_q,r (s = 1 / |row|)
@@ -230,10 +231,12 @@ __device__ void block_scan(int32_t* x, int n, bool reverse, int* part) {
 // of NSET threads.
 __global__ __launch_bounds__(NSET) void k_ragged_setup(const int32_t* cu, int n_seq, int T, int32_t* seq_start,
                                                       int32_t* seq_len, int32_t* chunk_off, int32_t* perm,
-                                                      int32_t* prefix, int32_t* ghist, int cpt, int ch) {
+                                                      int32_t* prefix, int32_t* ghist, int cpt, int ch,
+                                                      int32_t* row_groups, int wgs_per_seq, int cus) {
     __shared__ int part[NSET];
     __shared__ int scu[NSET + 1];
     __shared__ int shist[8192];
+    __shared__ int at[6];
     int32_t* hist = cpt + 2 <= 8192 ? shist : ghist;   // the histogram in LDS when it fits
     const int t = threadIdx.x;
     // offsets clamped into a partition of [0, T]: a serial walk by thread 0 over
@@ -260,6 +263,7 @@ __global__ __launch_bounds__(NSET) void k_ragged_setup(const int32_t* cu, int n_
         __syncthreads();
     }
     for (int c = t; c <= cpt + 1; c += NSET) hist[c] = 0;
+    if (t < 6) at[t] = 0;
     __syncthreads();
     for (int s = t; s < n_seq; s += NSET) atomicAdd(&hist[(seq_len[s] + ch - 1) / ch], 1);   // counts <= cpt
     __syncthreads();
@@ -267,8 +271,37 @@ __global__ __launch_bounds__(NSET) void k_ragged_setup(const int32_t* cu, int n_
     block_scan(hist, cpt + 1, true, part);
     for (int c = t; c <= cpt; c += NSET) prefix[c] = hist[c];
     __syncthreads();
-    for (int s = t; s < n_seq; s += NSET) perm[atomicAdd(&hist[(seq_len[s] + ch - 1) / ch], 1)] = s;
+    // With row_groups: at[i], the chunks of the sequence whose chain workgroups, w for each sequence, hold workgroup
+    // 0, cus - 1 and cus of the longest-first order (i = 0, 1, 2 with one group of state rows, 3, 4, 5 with two)
+    int rank[6];
+#pragma unroll
+    for (int i = 0; i < 6; ++i) {
+        const int w = i < 3 ? wgs_per_seq : wgs_per_seq / 2, wg = i % 3 == 0 ? 0 : i % 3 == 1 ? cus - 1 : cus;
+        rank[i] = row_groups ? wg / w : -1;   // past the last sequence: at stays 0
+    }
+    for (int s = t; s < n_seq; s += NSET) {
+        const int nc = (seq_len[s] + ch - 1) / ch, r = atomicAdd(&hist[nc], 1);
+        perm[r] = s;
+#pragma unroll
+        for (int i = 0; i < 6; ++i)
+            if (r == rank[i]) at[i] = nc;
+    }
     block_scan(prefix, cpt + 1, false, part);
+    if (!row_groups) return;
+    if (t == 0) {
+        // One or two groups, by the chunk steps of the CU that ends last: at least the longest sequence's, an even
+        // share of all, and, as workgroups start longest first, the last one of a first round with the first of the
+        // second.  A workgroup starts in the time of 6 steps, and a step of two groups counts 1.2 (it takes 1.3 times
+        // one of one group, which makes up for some of it by half the loads): of 38 calls timed both ways 2 took the
+        // slower form, by 1.7 % at most.  16 heads of 128, one and two groups: 4 prompts of 1000 tokens 50 and 38 us;
+        // of 4509 in all, 2987 the longest, 61 and 71; 8 heads, 8 prompts of 17481 and of 6766 tokens 89 and 94,
+        // 59 and 69.
+        const auto steps = [&](int i, int w) {
+            const auto with_start = [&](int k) { return at[k] > 0 ? at[k] + 6 : 0; };
+            return max((float)max(with_start(i), with_start(i + 1) + with_start(i + 2)), (float)(acc + 6 * n_seq) * w / cus);
+        };
+        row_groups[0] = 1.2f * steps(3, wgs_per_seq / 2) < steps(0, wgs_per_seq) ? 2 : 1;
+    }
 }
 
 // Stage rows [t0, t0+n) of two [*, H, D] io tensors (head h) into LDS tiles
@@ -1957,6 +1990,29 @@ __global__ __launch_bounds__(NT_CHAIN) __attribute__((amdgpu_waves_per_eu(1, 2))
     }
 }
 
+// The chain of packed prompts in two to three 16-row workgroups per CU: one or two groups of state rows each, as
+// k_ragged_setup found faster for the prompts' lengths.  The grid is that of one group; with two its rear half has
+// nothing to do.  Against a launch of the better form alone, which only the lengths tell (16 heads of 128): 4 prompts
+// of 1000 tokens, two groups, 39.0 -> 43.3 us (one group 50.8); of 4868 in all, 2965 the longest, one group, 60.1 -> 61.2
+// (two 69.5); 8 heads, 8 prompts of 8939, 62.7 -> 62.9 (73.9).  One group whose workgroups each went on to the next
+// slice from a counter, on the grid of two, took 41.1, 63.4 and 65.7.
+template <int DK, bool SNAP = false, bool NORM = false>
+__global__ __launch_bounds__(NT_CHAIN) __attribute__((amdgpu_waves_per_eu(1, 2))) void k_state_chain_packed_bf16(Params p) {
+    __shared__ union Lds {
+        __device__ Lds() {}
+        ChainLds<DK, 1> one;
+        ChainLds<DK, 2> two;
+    } lds;
+    if (tab(p.row_groups, 0) == 2) {
+        if (2 * blockIdx.x >= gridDim.x) return;
+        const Params& p2 = fresh_params();
+        state_chain_bf16<DK, 2, false, false, SNAP, NORM>(p2, blockIdx.x, lds.two);
+    } else {
+        const Params& p1 = fresh_params();
+        state_chain_bf16<DK, 1, false, false, SNAP, NORM>(p1, blockIdx.x, lds.one);
+    }
+}
+
 // ------------------------------------------------------------------ decode
 // One token per sequence.  LPR lanes hold one state row as float4s; rows of S
 // evolve independently: s_j <- alpha (s_j - beta (s_j.k) k) + beta v_j k.
@@ -2687,7 +2743,7 @@ bool ws_layout(int B, int T, int H, int dk, int dv, int n_seqs, int io, Layout* 
         L->meta = L->G = L->T = L->P = L->F = L->KQ = L->total = 0;
         return true;
     }
-    L->meta = 256;   // bytes [0, 8): the status word (gdn_workspace_status)
+    L->meta = 256;   // bytes [0, 8): the status word (gdn_workspace_status); [64, 68): Params::row_groups
     L->G = L->meta + (n_seqs > 0 ? round_up(((size_t)4 * (n_seqs + 1) + 2 * (size_t)(cpt + 2)) * sizeof(int32_t), 256) : 0);
     L->T = L->G + round_up(per * GS * sizeof(float), 256);
     const size_t tp = io == GDN_BF16 ? tp_elems<bf16_t>() : tp_elems<float>();
@@ -2728,7 +2784,7 @@ template <typename IO, int C, int DK>
 void launch_generic_c(const Params& p, long slots, hipStream_t st) {
     if (p.ragged)
         hipLaunchKernelGGL(k_ragged_setup, dim3(1), dim3(NSET), 0, st, p.cu, p.n_seq, p.T, p.seq_start, p.seq_len,
-                           p.chunk_off, p.seq_perm, p.cprefix, p.cprefix + (p.cpt + 2), p.cpt, C);
+                           p.chunk_off, p.seq_perm, p.cprefix, p.cprefix + (p.cpt + 2), p.cpt, C, (int32_t*)nullptr, 2, 1);
     if (slots > 0 && p.T > 0) {
         hipLaunchKernelGGL((k_gen_gram<IO, C, DK>), dim3((unsigned)(slots * p.H)), dim3(GEN_NT), 0, st, p);
         hipLaunchKernelGGL((k_gen_solve<C>), dim3((unsigned)(slots * p.H)), dim3(GEN_NT), 0, st, p);
@@ -2791,28 +2847,30 @@ uint64_t next_epoch() {
 // How the bf16 sequential form runs its wgs chain workgroups of 16 state rows (one per CU: their LDS).
 // One launch, the chunk terms formed beside the chain, while the chain leaves a quarter of the CUs free.
 bool one_launch(long wgs, long cus) { return cus - wgs >= 8 && 4 * (cus - wgs) >= cus; }
-// Dense input, otherwise: two groups of 16 rows per workgroup when that saves rounds, which is when one
-// group would need more than one: a chunk step of 32 state rows takes about 1.3 times one of 16.
+// Otherwise, dense input: two groups of 16 rows per workgroup when that saves rounds, which is when one group would need more
+// than one: a chunk step of 32 state rows takes about 1.3 times one of 16.
 bool two_row_groups(long wgs, long cus) { return wgs > cus; }
 
 template <typename IO, int DK, bool SNAP = false, bool NORM = false>
 void launch_prefill(Params p, long slots, hipStream_t st) {
+    const long cus = std::max(1, stream_cus(st)), wgs = (long)p.n_seq * p.H * (p.DV / SL);
+    const bool two = sizeof(IO) == 2 && (p.ragged ? wgs >= 3 * cus : two_row_groups(wgs, cus));
+    const bool by_length = sizeof(IO) == 2 && p.ragged && wgs >= 2 * cus && !two;
     if (p.ragged)
         hipLaunchKernelGGL(k_ragged_setup, dim3(1), dim3(NSET), 0, st, p.cu, p.n_seq, p.T, p.seq_start,
-                           p.seq_len, p.chunk_off, p.seq_perm, p.cprefix, p.cprefix + (p.cpt + 2), p.cpt, CH);
+                           p.seq_len, p.chunk_off, p.seq_perm, p.cprefix, p.cprefix + (p.cpt + 2), p.cpt, CH,
+                           by_length ? p.row_groups : nullptr, p.H * (p.DV / SL), (int)cus);
     if constexpr (sizeof(IO) == 2) {
         // one launch, or the chunk terms first (one-wave workgroups, eight per CU) and the chain
         // after, longest sequence first
-        const long nchain = (long)p.n_seq * p.H * (p.DV / SL);
         const long items = slots * p.H;
-        const long cus = stream_cus(st);
-        if (one_launch(nchain, cus) && items > 0) {
-            p.npw = (int)std::min(cus - nchain, items);
+        if (one_launch(wgs, cus) && items > 0) {
+            p.npw = (int)std::min(cus - wgs, items);
             p.xcd_items = !p.ragged && p.H % 8 == 0 && p.npw >= 8;
             if (p.xcd_items) p.npw &= ~7;
             p.term_waves = std::max(1, std::min(TERM_WAVES_MAX, (TERM_WAVES_ALL + p.npw / 2) / p.npw));
             p.epoch = next_epoch();
-            hipLaunchKernelGGL((k_prefill_fused_bf16<DK, SNAP, NORM>), dim3((unsigned)(p.npw + nchain)), dim3(NT_CHAIN), 0,
+            hipLaunchKernelGGL((k_prefill_fused_bf16<DK, SNAP, NORM>), dim3((unsigned)(p.npw + wgs)), dim3(NT_CHAIN), 0,
                                st, p);
             return;
         }
@@ -2827,18 +2885,19 @@ void launch_prefill(Params p, long slots, hipStream_t st) {
         // One and two row groups at 16 heads of 128: 2 x 4096 tokens, 256 and 128 workgroups: 71 and
         // 84 us; 3 x 1500 tokens, 384 and 192: 58 and 44.5; 4 x 1000: 46 and 35; 5 x 2000: 105 and 95; of
         // 64: 8 x 1280, 512 and 256: 52 and 42, 4 x 1000, 256 and 128: 24.6 and 27.4; with the input
-        // transforms or snapshots the same way (3 x 1500: 62 and 48, 64 and 52).  Packed prompts differ in
-        // length, so their workgroups spread better over the CUs than rounds say (3 prompts of 300 to
-        // 2000 tokens, 384 and 192: 47 and 52 us): there from two workgroups per CU on.
-        const long cus = std::max(1, stream_cus(st)), wgs = (long)p.n_seq * p.H * (p.DV / SL);
-        const bool two = p.ragged ? wgs >= 2 * cus : two_row_groups(wgs, cus);
-        if (two)
+        // transforms or snapshots the same way (3 x 1500: 62 and 48, 64 and 52).
+        // Packed prompts differ in length, so workgroups spread better over the CUs than rounds say: below two
+        // per CU one group (3 prompts of 300 to 2000 tokens, 384 and 192: 47 and 52 us), from three on two (16
+        // drawn sets of 7 and 8 prompts, 896 and 1024: 5 % slower to 27 % faster), between by their lengths.
+        if (by_length)
+            hipLaunchKernelGGL((k_state_chain_packed_bf16<DK, SNAP, NORM>), dim3((unsigned)wgs), dim3(NT_CHAIN), 0, st, p);
+        else if (two)
             hipLaunchKernelGGL((k_state_chain_bf16<DK, 2, SNAP, NORM>), dim3((unsigned)(wgs / 2)), dim3(NT_CHAIN), 0, st, p);
         else
             hipLaunchKernelGGL((k_state_chain_bf16<DK, 1, SNAP, NORM>), dim3((unsigned)wgs), dim3(NT_CHAIN), 0, st, p);
     }
     else
-        hipLaunchKernelGGL((k_state_chain<DK, SNAP>), dim3((unsigned)(p.n_seq * p.H * (p.DV / SL))), dim3(NT_CHAIN_F32), 0, st, p);
+        hipLaunchKernelGGL((k_state_chain<DK, SNAP>), dim3((unsigned)wgs), dim3(NT_CHAIN_F32), 0, st, p);
 }
 
 // ---- evaluation plans: sequential chain, segment-parallel (narrow and wide); workspace; launches
@@ -3251,6 +3310,7 @@ static gdn_status prefill(const void* q, const void* k, const void* v, const flo
     p.chunk_off = p.ragged ? p.seq_len + (n_seqs + 1) : nullptr;
     p.seq_perm = p.ragged ? p.chunk_off + (n_seqs + 1) : nullptr;
     p.cprefix = p.ragged ? p.seq_perm + (n_seqs + 1) : nullptr;
+    p.row_groups = reinterpret_cast<int32_t*>(ws + 64);
     p.cpt = (T + C - 1) / C;
     p.wsG = reinterpret_cast<float*>(ws + L.G);
     p.wsT = ws + L.T;
