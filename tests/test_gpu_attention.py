@@ -151,11 +151,12 @@ def test_attention_packed_sequences(d, H, Hkv):
     assert worst < TOL
 
 
+@pytest.mark.parametrize("d", [64, 128])
 @pytest.mark.parametrize("n,clamped", [(64, False), (65, False), (5, True)])
-def test_attention_packed_block_order(n, clamped):
+def test_attention_packed_block_order(n, clamped, d):
     """Large packed grids take the blocks of up to 64 sequences longest first and those of more sequence by
     sequence; offsets outside the contract are clamped into a nondecreasing partition of [0, T] either way."""
-    H, Hkv, d, T = 64, 8, 128, 2400
+    H, Hkv, T = 64, 8, 2400
     if clamped:
         cu = np.array([0, 700, 300, 5000, -3, 2400], dtype=np.int32)
     else:
