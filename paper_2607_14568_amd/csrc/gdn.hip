@@ -94,8 +94,6 @@ __device__ __forceinline__ floatx4 f4(const void* ptr) { return *reinterpret_cas
 // + e%4 -- exactly the rows an MFMA accumulator tile pair holds in that lane.
 constexpr int NFRAG = 6;
 __host__ __device__ constexpr int frag_id(int mt, int kk) { return mt < 2 ? mt : 2 + 2 * (mt - 2) + kk; }
-__device__ __forceinline__ int frag_mt(int f) { return f < 2 ? f : 2 + ((f - 2) >> 1); }
-__device__ __forceinline__ int frag_kk(int f) { return f < 2 ? 0 : ((f - 2) & 1); }
 
 // Elements per (chunk, head) slot of T and of P in the workspace.
 template <typename IO> __host__ __device__ constexpr int tp_elems() { return sizeof(IO) == 2 ? NFRAG * 64 * 8 : CH * CH; }
@@ -130,7 +128,7 @@ struct Params {
                          // in fp32 io), and with PRE_L2 gamma_r s_k,r and gamma_r s_q,r (s = 1 / |row|)
     void* wsT;           // [slot][H]: bf16 io W fragments; fp32 io T as high and low bf16 64 x 64 tiles
     void* wsP;           // [slot][H]: bf16 io P' fragments; fp32 io P as high and low bf16 64 x 64 tiles
-    void* wsKQ;          // fp32 io: [slot][H][4][64][dk] bf16, K and Q as high and low parts (chain LDS order)
+    void* wsKQ;          // fp32 io: [slot][H][4][64][dk] bf16, K (chain LDS order) and Q (operand order), high and low parts
     uint64_t* flags;     // fused bf16 launch: [slot][H], = epoch once the slot's chunk terms are stored
     uint64_t epoch;      // per-call tag of those flags
     uint64_t* status;    // fused bf16 launch: the workspace's status word (= epoch when a wait gave up)
@@ -301,36 +299,6 @@ __global__ __launch_bounds__(NSET) void k_ragged_setup(const int32_t* cu, int n_
             return max((float)max(with_start(i), with_start(i + 1) + with_start(i + 2)), (float)(acc + 6 * n_seq) * w / cus);
         };
         row_groups[0] = 1.2f * steps(3, wgs_per_seq / 2) < steps(0, wgs_per_seq) ? 2 : 1;
-    }
-}
-
-// Stage rows [t0, t0+n) of two [*, H, D] io tensors (head h) into LDS tiles
-// [64][LD]; rows n..63 are zero.  Every load is issued before the first LDS
-// store, so the tiles cost one memory latency rather than one per pass.
-template <typename IO, int D, int LD>
-__device__ __forceinline__ void stage_rows2(IO (*dA)[LD], const IO* sA, IO (*dB)[LD], const IO* sB, long t0, int n,
-                                            int H, int h) {
-    constexpr int VE = 16 / sizeof(IO);
-    constexpr int VPR = D / VE;
-    constexpr int NPT = (CH * VPR + NT - 1) / NT;
-    uint4 a[NPT], b[NPT];
-#pragma unroll
-    for (int j = 0; j < NPT; ++j) {
-        const int i = threadIdx.x + NT * j, r = i / VPR, cv = i % VPR;
-        a[j] = b[j] = make_uint4(0, 0, 0, 0);
-        if (i < CH * VPR && r < n) {
-            const long off = ((t0 + r) * H + h) * (long)D + cv * VE;
-            a[j] = *reinterpret_cast<const uint4*>(sA + off);
-            b[j] = *reinterpret_cast<const uint4*>(sB + off);
-        }
-    }
-#pragma unroll
-    for (int j = 0; j < NPT; ++j) {
-        const int i = threadIdx.x + NT * j, r = i / VPR, cv = i % VPR;
-        if (i < CH * VPR) {
-            *reinterpret_cast<uint4*>(&dA[r][cv * VE]) = a[j];
-            *reinterpret_cast<uint4*>(&dB[r][cv * VE]) = b[j];
-        }
     }
 }
 
@@ -2750,7 +2718,7 @@ bool ws_layout(int B, int T, int H, int dk, int dv, int n_seqs, int io, Layout* 
     L->P = L->T + round_up(per * tp * esz, 256);
     L->F = L->P + round_up(per * tp * esz, 256);
     L->KQ = L->F + (io == GDN_BF16 ? round_up(per * sizeof(uint64_t), 256) : 0);
-    // fp32 io: K and Q of every (chunk slot, head) as high and low bf16 parts, in the chain's LDS order
+    // fp32 io: K and Q of every (chunk slot, head) as high and low bf16 parts, in the order the chain reads them
     L->total = L->KQ + (io == GDN_BF16 ? 0 : round_up(per * 4 * CH * (size_t)dk * sizeof(bf16_t), 256));
     return true;
 }
