@@ -122,7 +122,6 @@ struct Params {
     int32_t* chunk_off;  // [n_seq + 1], first chunk slot of each sequence
     int32_t* seq_perm;   // ragged: sequences by chunk count, longest first
     int32_t* cprefix;    // ragged: [cpt + 1] (sequence, chunk index < c) pair counts
-    int32_t* row_groups; // k_state_chain_packed_bf16: groups of 16 state rows per workgroup (from k_ragged_setup)
     int cpt;             // chunks of the longest possible sequence
     float* wsG;          // [slot][H][GS]: gamma_r = exp(G_r), D_r = exp(G_n - G_r) (times s_k,r with PRE_L2
                          // in fp32 io), and with PRE_L2 gamma_r s_k,r and gamma_r s_q,r (s = 1 / |row|)
@@ -131,7 +130,7 @@ struct Params {
     void* wsKQ;          // fp32 io: [slot][H][4][64][dk] bf16, K (chain LDS order) and Q (operand order), high and low parts
     uint64_t* flags;     // fused bf16 launch: [slot][H], = epoch once the slot's chunk terms are stored
     uint64_t epoch;      // per-call tag of those flags
-    uint64_t* status;    // fused bf16 launch: the workspace's status word (= epoch when a wait gave up)
+    uint64_t* status;    // the workspace's status word (fused bf16 launch: = epoch when a wait gave up) and header
     int wait_bound;      // fused bf16 launch: most flag polls of one chain workgroup in the call
     int withhold;        // fused bf16 launch: chunk terms publish nothing (GDN_TEST_WITHHOLD)
     int npw;             // fused bf16 launch: chunk-terms workgroups ahead of the chain workgroups
@@ -143,6 +142,10 @@ struct Params {
     int snap_every;      // ... after every snap_every chunks of a sequence, strictly inside it
     int n_snap;
 };
+
+// Groups of 16 state rows per workgroup of k_state_chain_packed_bf16, in the workspace's header (from k_ragged_setup;
+// no field of its own: with 8 bytes more in Params 256 tokens, 2 heads of 64 took 16.5 us, not 16.3).
+__host__ __device__ __forceinline__ int32_t* row_groups(const Params& p) { return reinterpret_cast<int32_t*>(p.status) + 16; }
 
 // Entry i of a sequence table, read where every lane of the wave reads the same
 // entry: held in a scalar register, so descriptors built from it stay scalar (a
@@ -1971,7 +1974,7 @@ __global__ __launch_bounds__(NT_CHAIN) __attribute__((amdgpu_waves_per_eu(1, 2))
         ChainLds<DK, 1> one;
         ChainLds<DK, 2> two;
     } lds;
-    if (tab(p.row_groups, 0) == 2) {
+    if (tab(row_groups(p), 0) == 2) {
         if (2 * blockIdx.x >= gridDim.x) return;
         const Params& p2 = fresh_params();
         state_chain_bf16<DK, 2, false, false, SNAP, NORM>(p2, blockIdx.x, lds.two);
@@ -2711,7 +2714,7 @@ bool ws_layout(int B, int T, int H, int dk, int dv, int n_seqs, int io, Layout* 
         L->meta = L->G = L->T = L->P = L->F = L->KQ = L->total = 0;
         return true;
     }
-    L->meta = 256;   // bytes [0, 8): the status word (gdn_workspace_status); [64, 68): Params::row_groups
+    L->meta = 256;   // bytes [0, 8): the status word (gdn_workspace_status); [64, 68): row_groups()
     L->G = L->meta + (n_seqs > 0 ? round_up(((size_t)4 * (n_seqs + 1) + 2 * (size_t)(cpt + 2)) * sizeof(int32_t), 256) : 0);
     L->T = L->G + round_up(per * GS * sizeof(float), 256);
     const size_t tp = io == GDN_BF16 ? tp_elems<bf16_t>() : tp_elems<float>();
@@ -2821,13 +2824,14 @@ bool two_row_groups(long wgs, long cus) { return wgs > cus; }
 
 template <typename IO, int DK, bool SNAP = false, bool NORM = false>
 void launch_prefill(Params p, long slots, hipStream_t st) {
-    const long cus = std::max(1, stream_cus(st)), wgs = (long)p.n_seq * p.H * (p.DV / SL);
+    const long cus = sizeof(IO) == 2 ? std::max(1, stream_cus(st)) : 1;   // (fp32 io has one form)
+    const long wgs = (long)p.n_seq * p.H * (p.DV / SL);
     const bool two = sizeof(IO) == 2 && (p.ragged ? wgs >= 3 * cus : two_row_groups(wgs, cus));
     const bool by_length = sizeof(IO) == 2 && p.ragged && wgs >= 2 * cus && !two;
     if (p.ragged)
         hipLaunchKernelGGL(k_ragged_setup, dim3(1), dim3(NSET), 0, st, p.cu, p.n_seq, p.T, p.seq_start,
                            p.seq_len, p.chunk_off, p.seq_perm, p.cprefix, p.cprefix + (p.cpt + 2), p.cpt, CH,
-                           by_length ? p.row_groups : nullptr, p.H * (p.DV / SL), (int)cus);
+                           by_length ? row_groups(p) : nullptr, p.H * (p.DV / SL), (int)cus);
     if constexpr (sizeof(IO) == 2) {
         // one launch, or the chunk terms first (one-wave workgroups, eight per CU) and the chain
         // after, longest sequence first
@@ -3278,7 +3282,6 @@ static gdn_status prefill(const void* q, const void* k, const void* v, const flo
     p.chunk_off = p.ragged ? p.seq_len + (n_seqs + 1) : nullptr;
     p.seq_perm = p.ragged ? p.chunk_off + (n_seqs + 1) : nullptr;
     p.cprefix = p.ragged ? p.seq_perm + (n_seqs + 1) : nullptr;
-    p.row_groups = reinterpret_cast<int32_t*>(ws + 64);
     p.cpt = (T + C - 1) / C;
     p.wsG = reinterpret_cast<float*>(ws + L.G);
     p.wsT = ws + L.T;
