@@ -2815,6 +2815,20 @@ uint64_t next_epoch() {
     return (epoch_salt() << 32) | (uint32_t)(counter.fetch_add(1, std::memory_order_relaxed) + 1);
 }
 
+// Is the stream being captured into a graph?  (The null stream cannot be.)
+bool capturing(hipStream_t st) {
+    hipStreamCaptureStatus s = hipStreamCaptureStatusNone;
+    if (st != nullptr && hipStreamIsCapturing(st, &s) != hipSuccess) (void)hipGetLastError();
+    return s != hipStreamCaptureStatusNone;
+}
+
+// A captured one-launch call carries one tag, so from the second replay on its flags would be found set before the
+// chunk terms are formed: they are cleared ahead of it.
+__global__ __launch_bounds__(NT) void k_clear_flags(uint64_t* flags, long n) {
+    const long i = (long)blockIdx.x * NT + threadIdx.x;
+    if (i < n) flags[i] = 0;
+}
+
 // How the bf16 sequential form runs its wgs chain workgroups of 16 state rows (one per CU: their LDS).
 // One launch, the chunk terms formed beside the chain, while the chain leaves a quarter of the CUs free.
 bool one_launch(long wgs, long cus) { return cus - wgs >= 8 && 4 * (cus - wgs) >= cus; }
@@ -2842,6 +2856,8 @@ void launch_prefill(Params p, long slots, hipStream_t st) {
             if (p.xcd_items) p.npw &= ~7;
             p.term_waves = std::max(1, std::min(TERM_WAVES_MAX, (TERM_WAVES_ALL + p.npw / 2) / p.npw));
             p.epoch = next_epoch();
+            if (capturing(st))
+                hipLaunchKernelGGL(k_clear_flags, dim3((unsigned)((items + NT - 1) / NT)), dim3(NT), 0, st, p.flags, items);
             hipLaunchKernelGGL((k_prefill_fused_bf16<DK, SNAP, NORM>), dim3((unsigned)(p.npw + wgs)), dim3(NT_CHAIN), 0,
                                st, p);
             return;
