@@ -239,6 +239,8 @@ __global__ __launch_bounds__(NSET) void k_ragged_setup(const int32_t* cu, int n_
     __shared__ int shist[8192];
     __shared__ int at[6];
     int32_t* hist = cpt + 2 <= 8192 ? shist : ghist;   // the histogram in LDS when it fits
+    // (hist is a generic pointer, and the hardware finds the memory it is in by the base address alone: read hist[c]
+    // with no neighbour, hist[c - 1] makes the compiler take a base one below LDS for c = 0, which faults)
     const int t = threadIdx.x;
     // offsets clamped into a partition of [0, T]: a serial walk by thread 0 over
     // blocks of offsets that all threads fetch at once
