@@ -2417,7 +2417,7 @@ template <int DH> struct AttnLds {
     bf16_t v[2][AKB * DH];
 };
 
-template <int DH, int QT>
+template <int DH, int QT, bool ONE = false>   // ONE: at most one workgroup per CU
 __global__ __launch_bounds__(NT_ATT / QT) __attribute__((amdgpu_waves_per_eu(4 / QT))) void k_attn_causal(AttnParams p) {
     constexpr int NW = NT_ATT / 64 / QT;   // waves; each holds QT tiles of 16 queries
     constexpr int NCH = DH / 8;         // 16-byte chunks per row
@@ -2533,10 +2533,11 @@ __global__ __launch_bounds__(NT_ATT / QT) __attribute__((amdgpu_waves_per_eu(4 /
         constexpr int sl = decltype(SLOT)::value;
         const auto rk = rows_rsrc(kbase, rsk, j * AKB, AKB);
         const auto rv = rows_rsrc(vbase, rsk, j * AKB, AKB);
-        if constexpr (SMALL) {
-            // one loop with offsets formed in place: 16 heads, 1000, 1500 and 2048 tokens 24.3, 34.3 and
-            // 45.2 us against 24.6, 34.7 and 45.7 with the branch-free copies below (2500 and 3000 57.6 and
-            // 70.4 against 57.3 and 70.1); the other two forms are 2 % faster with those
+        if constexpr (SMALL && ONE) {
+            // one loop with offsets formed in place: 16 heads, 1000, 1500 and 2048 tokens (a workgroup per CU or
+            // fewer) 24.2, 34.2 and 45.1 us against 24.6, 34.7 and 45.7 with the branch-free copies below; 2500, 3000
+            // and 4500 57.5, 70.2 and 117.3 against 57.2, 70.0 and 117.0, packed 1000, 2000 and 300 47.0 and 46.6 (on
+            // inputs still in the caches the branch-free copies are 0.5 % faster at every size)
 #pragma unroll
             for (int c = wave; c < 2 * NCW * NW; c += NW) {
                 const int cc = c % (NCW * NW), r = RPI * cc + lane / NCH;
@@ -3152,7 +3153,10 @@ void launch_attention(AttnParams a, hipStream_t st) {
             return;
         }
     }
-    hipLaunchKernelGGL((k_attn_causal<DH, 1>), dim3((unsigned)wgs), dim3(NT_ATT), 0, st, a);
+    if (DH == 128 && wgs <= stream_cus(st))
+        hipLaunchKernelGGL((k_attn_causal<DH, 1, DH == 128>), dim3((unsigned)wgs), dim3(NT_ATT), 0, st, a);
+    else
+        hipLaunchKernelGGL((k_attn_causal<DH, 1>), dim3((unsigned)wgs), dim3(NT_ATT), 0, st, a);
 }
 
 }  // namespace
